@@ -93,22 +93,21 @@ extern "C" {
 /* ---- options ---------------------------------------------------------- */
 enum ccpt_mode { CCPT_MODE_CCU = 0, CCPT_MODE_CCSN = 1 };
 
-/* arithmetic of the correlation and the upsampled matrix DFT (the Newton
-   refinement is FP64 in every mode) */
+/* arithmetic of the correlation and the upsampled grid (the correlation's
+   expansion on the window and the Newton refinement are FP64 in every mode) */
 enum ccpt_precision {
-  CCPT_PREC_FP32 = 0,   /* FP32 FFTs, FP32 matrix cores */
-  CCPT_PREC_BF16X2 = 1, /* FP32 FFTs; DFT operands split into bf16 hi + lo,
-                           three bf16 products accumulated in FP32 */
-  CCPT_PREC_FP16X2 = 2, /* FP32 FFTs; DFT operands split into fp16 hi + lo
-                           (about 22 bits) under power-of-two scales, three
-                           fp16 products accumulated in FP32.  256 x 256
+  CCPT_PREC_FP32 = 0,   /* FP32 FFTs, FP32 grid values */
+  CCPT_PREC_BF16X2 = 1, /* least precision asked of the grid values: bf16 hi +
+                           lo products.  Computed as FP32 (which is faster) */
+  CCPT_PREC_FP16X2 = 2, /* least precision asked of the grid values: fp16 hi +
+                           lo products.  Computed as FP32 with the one-kernel
+                           correlation for launches of any size: 256 x 256
                            frames of uint16 or float32 with an even pitch
-                           only (the one-kernel correlation): other shapes
-                           and pixel layouts give CCPT_E_UNSUPPORTED */
+                           only; other shapes and pixel layouts give
+                           CCPT_E_UNSUPPORTED */
   CCPT_PREC_FP64 = 3    /* FFTs, cross-power spectrum, integer peak and the
-                           upsampled DFT all in FP64 (vector units): the
-                           accuracy mode, for agreement with an FP64
-                           definition well below 1e-9 px */
+                           grid all in FP64: the accuracy mode, for agreement
+                           with an FP64 definition well below 1e-9 px */
 };
 
 /* pixel types: uint16 (12-bit cameras), float32, float64 */
@@ -132,8 +131,8 @@ enum ccpt_stage {
   CCPT_STAGE_ROWS_FWD = 1, /* prologue + row r2c FFTs */
   CCPT_STAGE_COLS = 2,     /* column FFTs, cross-power spectrum, inverse column FFTs */
   CCPT_STAGE_ROWS_INV = 3, /* row c2r FFTs + integer peak */
-  CCPT_STAGE_UPDFT = 4,    /* upsampled matrix DFT + grid maximum */
-  CCPT_STAGE_NEWTON = 5,   /* FP64 Newton refinement + result */
+  CCPT_STAGE_UPDFT = 4,    /* FP64 expansion of the correlation on the window */
+  CCPT_STAGE_NEWTON = 5,   /* upsampled-grid maximum + FP64 Newton refinement + result */
   CCPT_STAGE_GRAD = 6,     /* all kernels of ccpt_track_grad */
   CCPT_STAGE_XCORR = 7,    /* stages 1-3 in one kernel (256 x 256 frames) */
   CCPT_NUM_STAGES = 8
@@ -219,9 +218,9 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
    hipMalloc/hipFree.  `rois` is a host array, consumed before the call
    returns (its copy to the scratch is enqueued from pageable memory, so the
    call is not meant for stream capture).  Frames run in chunks that fit the
-   scratch (about 80 frames of 256x256 in split precision); no graphs,
-   second stream or profiling events; small launches take the unsplit
-   kernels, so results equal ccpt_track_batch's to rounding (<= 1e-6 px;
+   scratch (about 120 frames of 256x256); no graphs,
+   second stream or profiling events; launches of another size sum in
+   another order, so results equal ccpt_track_batch's to rounding (<= 1e-6 px;
    integer peak and grid index identical).  The context must already hold
    its references (set by ccpt_set_reference, which allocates).  All calls
    on one GPU share its scratch, which keeps the last call's contents: calls
@@ -329,8 +328,8 @@ int ccpt_schedule(ccpt_ctx* ctx, int n, int* chunk, int set);
    arithmetic of a launch of a given size. */
 typedef struct ccpt_plan {
   int chunk;        /* frames per launch chunk; 0 = default */
-  int split_blocks; /* FP32 matrix DFT: launches of fewer than this many 32-row grid
-                       tiles split Stage A over 8 ky slices added in a fixed order
+  int split_blocks; /* launches of fewer than this many frames spread each frame's window
+                       expansion over several blocks, added in a fixed order
                        (latency); -1 = default (128), 0 = never; at most 512 */
   int fused_min;    /* 256 x 256 frames: launches of at least this many frames take
                        the one-kernel correlation stage (one frame per CU), smaller

@@ -15,8 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libccpt.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["api.cpp", "xcorr.hip", "updft.hip", "updft64.hip", "newton.hip", "grad.hip",
-           "reference.hip", "scratch.hip", "xcorr256.hip"]
+SOURCES = ["api.cpp", "xcorr.hip", "xcorr256.hip", "refine.hip", "grad.hip", "reference.hip",
+           "scratch.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950",

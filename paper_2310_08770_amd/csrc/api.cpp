@@ -55,14 +55,12 @@ int shape_code(int ny, int nx) {
 
 struct SizeTables {
   float2* tw = nullptr;  // N
-  void* ky = nullptr;
-  void* wb = nullptr;
-  unsigned* kfold = nullptr;  // split precision, N >= kWideMinN
-  int Mp = 0;
+  double2* gy = nullptr;
+  double2* gx = nullptr;
+  double* gxn = nullptr;
+  int ksteps = 0;
   // FP64 mode
   double2* tw64 = nullptr;  // N
-  double2* ky64 = nullptr;  // [Mp][N]
-  double2* wb64 = nullptr;  // [N/2+1][Mp]
 };
 
 struct Ref {
@@ -76,7 +74,7 @@ struct Ref {
 // Launch plan of one frame shape (ccpt_plan): chunk size and block plans.
 struct Schedule {
   int chunk = 0;          // frames per launch chunk (0 = default)
-  int split_blocks = -1;  // FP32: split Stage A below this many row tiles per launch (-1: default)
+  int split_blocks = -1;  // spread a frame over blocks in launches of fewer than this many frames (-1: default)
   int fused_min = -1;     // 256x256: one-kernel correlation from this many frames (-1: default)
 };
 
@@ -99,6 +97,10 @@ struct ccpt_ctx {
   ccpt_options o{};
   int M = 0, c = 0;
   std::map<int, SizeTables> tables;
+  // window expansion: half width and the grid's Chebyshev tables
+  double half = 0.0;
+  float* tf = nullptr;
+  double* td = nullptr;
   std::vector<Ref> refs;
   std::map<int, Schedule> sched;
   // workspace
@@ -129,27 +131,21 @@ struct ccpt_ctx {
   hipEvent_t small_evt = nullptr;
   void* acc_buf = nullptr;
   size_t acc_cap = 0;
-  // FP32 split-K partials of small launches
-  void* ypart = nullptr;
-  size_t ypart_cap = 0;
   // per-frame states of a chunk: kept in the initial state between chunks by
   // the Newton kernel; re-initialised after a failed launch
   FrameState* st_buf = nullptr;
   size_t st_cap = 0;
   bool st_dirty = true;
-  // partial Newton models of small launches
-  void* nparts = nullptr;
-  size_t nparts_cap = 0;
   // chunk slots: a group of several chunks runs them alternately on the
-  // caller's stream and `aux`, each slot with its own part of the workspace,
-  // frame states, split-K and Newton partials (strides below, per slot)
+  // caller's stream and `aux`, each slot with its own part of the workspace
+  // and frame states (strides below, per slot)
   hipStream_t aux = nullptr;
   hipEvent_t fork_evt = nullptr, join_evt = nullptr;
-  size_t slot_ws = 0, slot_st = 0, slot_ypart = 0;
+  size_t slot_ws = 0, slot_st = 0;
   // concurrent size groups: lane 0 is the caller's stream, lanes 1.. these
   // context-owned streams (default priority), forked from and joined back
-  // into the caller's stream by events; each lane has its own workspace,
-  // frame states, split-K and Newton partials
+  // into the caller's stream by events; each lane has its own workspace and
+  // frame states
   hipStream_t lane_s[kMaxLanes - 1] = {};
   hipEvent_t lane_evt[kMaxLanes - 1] = {};
   int lanes = 0;  // most lanes a call uses (0: kMaxLanes)
@@ -214,36 +210,34 @@ int upload(ccpt_ctx* ctx, T*& dst, const std::vector<T>& src) {
   return CCPT_OK;
 }
 
+void free_tables(SizeTables& t) {
+  for (void* p : {(void*)t.tw, (void*)t.gy, (void*)t.gx, (void*)t.gxn, (void*)t.tw64})
+    if (p) (void)hipFree(p);
+}
+
 int ensure_tables(ccpt_ctx* ctx, int code) {
   const int key = table_key(code);
   if (ctx->tables.count(key)) return CCPT_OK;
   const int n = code_ny(code), nx = code_nx(code);
   SizeTables t;
-  // the FP64 mode keeps the FP32 tables too (twiddles of the adjoint and Fisher paths)
-  HostTables h = build_tables(n, nx, ctx->o.upsample, ctx->M, ctx->c,
-                              fp64(ctx) ? CCPT_PREC_FP32 : ctx->o.precision);
-  t.Mp = h.Mp;
-  HIP_CHECK(ctx, hipMalloc(&t.tw, h.tw.size() * sizeof(float2)));
-  HIP_CHECK(ctx, hipMemcpy(t.tw, h.tw.data(), h.tw.size() * sizeof(float2), hipMemcpyHostToDevice));
-  HIP_CHECK(ctx, hipMalloc(&t.ky, h.ky.size()));
-  HIP_CHECK(ctx, hipMemcpy(t.ky, h.ky.data(), h.ky.size(), hipMemcpyHostToDevice));
-  HIP_CHECK(ctx, hipMalloc(&t.wb, h.wb.size()));
-  HIP_CHECK(ctx, hipMemcpy(t.wb, h.wb.data(), h.wb.size(), hipMemcpyHostToDevice));
-  if (fp64(ctx)) {
-    HostTables64 h64 = build_tables64(n, ctx->o.upsample, ctx->M, ctx->c, t.Mp);
-    int rc = upload(ctx, t.tw64, h64.tw);
-    if (!rc) rc = upload(ctx, t.ky64, h64.ky);
-    if (!rc) rc = upload(ctx, t.wb64, h64.wb);
-    if (rc) return rc;
+  const std::vector<double2> tw = twiddles(n);
+  std::vector<float2> tw32(n);
+  for (int m = 0; m < n; ++m) tw32[m] = make_float2((float)tw[m].x, (float)tw[m].y);
+  const ShapeTables h = build_shape_tables(n, nx, ctx->half);
+  t.ksteps = h.ksteps;
+  int rc = upload(ctx, t.tw, tw32);
+  if (!rc) rc = upload(ctx, t.gy, h.gy);
+  if (!rc) rc = upload(ctx, t.gx, h.gx);
+  if (!rc) rc = upload(ctx, t.gxn, h.gxn);
+  if (!rc && fp64(ctx)) rc = upload(ctx, t.tw64, tw);
+  if (!rc && !ctx->tf) {
+    const GridTables g = build_grid_tables(ctx->o.upsample, ctx->M, ctx->c, ctx->half);
+    rc = upload(ctx, ctx->tf, g.tf);
+    if (!rc) rc = upload(ctx, ctx->td, g.td);
   }
-  if (split(ctx) && nx >= kWideMinN) {
-    const size_t words = (size_t)n * 2 * kfold_rows(t.Mp) * xb_pitch(n);
-    if (hipMalloc(&t.kfold, words * sizeof(unsigned)) != hipSuccess)
-      return fail(ctx, CCPT_E_NOMEM, "folded table of %zu bytes", words * sizeof(unsigned));
-    if (launch_build_kfold(t.kfold, n, ctx->o.upsample, ctx->M, ctx->c, kfold_rows(t.Mp),
-                           ctx->o.precision == CCPT_PREC_FP16X2 ? 1 : 0, nullptr))
-      return fail(ctx, CCPT_E_HIP, "folded table launch failed");
-    HIP_CHECK(ctx, hipDeviceSynchronize());
+  if (rc) {
+    free_tables(t);
+    return rc;
   }
   ctx->tables[key] = t;
   return CCPT_OK;
@@ -273,24 +267,38 @@ int ensure_ws(ccpt_ctx* ctx, size_t bytes) {
   return CCPT_OK;
 }
 
-// Half-spectrum elements and split-precision words of one frame (shape code).
+// Half-spectrum elements of one frame (shape code).
 size_t spec_elems(int code) { return (size_t)code_ny(code) * (code_nx(code) / 2 + 1); }
 
-size_t split_words(int code) { return (size_t)2 * (code_nx(code) / 2) * xb_pitch(code_ny(code)); }
+// Workspace of one frame: the row-pass intermediate T, whose memory the window
+// coefficients take over once the correlation is done, and the spectrum X.
+size_t t_bytes(int n, int precision) {
+  const size_t el = precision == CCPT_PREC_FP64 ? sizeof(double2) : sizeof(float2);
+  const size_t coef = (size_t)window_tiles(code_nx(n)) * kChebN * kChebN * sizeof(double);
+  return (std::max(spec_elems(n) * el, coef) + 15) / 16 * 16;
+}
 
 size_t frame_ws_bytes(int n, int precision) {
   if (precision == CCPT_PREC_FP64)
-    return 2 * spec_elems(n) * sizeof(double2) + (size_t)(n / row_block64(n)) * sizeof(PeakCand);
-  size_t b = 2 * spec_elems(n) * sizeof(float2);
-  if (precision == CCPT_PREC_BF16X2 || precision == CCPT_PREC_FP16X2)
-    b += split_words(n) * sizeof(unsigned) + (size_t)code_ny(n) * sizeof(float2);  // Xb, Zc
-  return b;
+    return t_bytes(n, precision) + spec_elems(n) * sizeof(double2) +
+           (size_t)(n / row_block64(n)) * sizeof(PeakCand);
+  return t_bytes(n, precision) + spec_elems(n) * sizeof(float2);
 }
 
+// Default frames per chunk: 192 MB of spectra, well inside the 256 MB
+// Infinity Cache.  The split precisions count a second copy of the spectrum,
+// which they no longer keep: 256 x 256 groups take the one-kernel correlation
+// or the three passes by the size of their chunks, and a chunk of another
+// size would change which frames' sums run in which order.
 int default_chunk(int n, int precision) {
-  // keep the chunk's spectra well inside the 256 MB Infinity Cache
   const size_t budget = (size_t)192 << 20;
-  int c = (int)(budget / frame_ws_bytes(n, precision));
+  size_t b = 2 * spec_elems(n) * (precision == CCPT_PREC_FP64 ? sizeof(double2) : sizeof(float2));
+  if (precision == CCPT_PREC_FP64)
+    b += (size_t)(n / row_block64(n)) * sizeof(PeakCand);
+  else if (precision != CCPT_PREC_FP32)
+    b += (size_t)code_nx(n) * ((code_ny(n) + 31) / 32 * 32) * sizeof(unsigned) +
+         (size_t)code_ny(n) * sizeof(float2);
+  int c = (int)(budget / b);
   return std::max(1, std::min(c, 4096));
 }
 
@@ -303,7 +311,18 @@ int chunk_for(const ccpt_ctx* ctx, int n) {
 int split_blocks_for(const ccpt_ctx* ctx, int n) {
   auto it = ctx->sched.find(n);
   if (it != ctx->sched.end() && it->second.split_blocks >= 0) return it->second.split_blocks;
-  return kSplitMaxBlocks;
+  return kSplitBlocks;
+}
+
+// Blocks that share one frame's coefficient pass in a launch of `count`
+// frames: one from split_blocks frames on (128 blocks of four waves: half the
+// CUs, but nothing to add up afterwards), four down to half that, below it one
+// per 16 spectrum columns.  The sums' order follows the number of blocks, so
+// it changes only at these two lines.
+int window_parts(const ccpt_ctx* ctx, int n, int count) {
+  const int sb = split_blocks_for(ctx, n), tiles = window_tiles(code_nx(n));
+  if (count >= sb) return 1;
+  return count >= sb / 2 ? std::min(tiles, 4) : tiles;
 }
 
 int fused_min_for(const ccpt_ctx* ctx, int n) {
@@ -321,9 +340,6 @@ struct CallMem {
   size_t slot_ws = 0;
   FrameState* st = nullptr;    // frame states, slot_st entries per slot
   size_t slot_st = 0;
-  void* ypart = nullptr;       // FP32 split-K partials, slot_ypart bytes per slot (or none)
-  size_t slot_ypart = 0;
-  void* nparts = nullptr;      // Newton partial models per slot (or none)
   size_t chunk_bytes = 0;      // > 0: chunks limited to this much workspace
   bool slots = true;           // two chunk slots allowed (CCPT_FLAG_STREAMS)
   bool mark = true;            // profiling events allowed
@@ -336,9 +352,6 @@ CallMem ctx_mem(ccpt_ctx* ctx) {
   m.slot_ws = ctx->slot_ws;
   m.st = ctx->st_buf;
   m.slot_st = ctx->slot_st;
-  m.ypart = ctx->ypart;
-  m.slot_ypart = ctx->slot_ypart;
-  m.nparts = ctx->nparts;
   m.st_dirty = &ctx->st_dirty;
   return m;
 }
@@ -348,27 +361,21 @@ CallMem ctx_mem(ccpt_ctx* ctx) {
 void carve(ccpt_ctx* ctx, const CallMem& mem, int n, int chunk, int slot, GroupParams& g) {
   const size_t spec = spec_elems(n);
   char* ws = mem.ws + slot * mem.slot_ws;
+  char* x = ws + t_bytes(n, ctx->o.precision) * chunk;
   g.st = mem.st + slot * mem.slot_st;
+  g.coef = (double*)ws;
+  g.T = g.X = nullptr;
+  g.T64 = g.X64 = nullptr;
+  g.cand = nullptr;
   if (fp64(ctx)) {
-    g.T = g.X = nullptr;
-    g.Xb = nullptr;
     g.T64 = (double2*)ws;
-    g.X64 = g.T64 + spec * chunk;
+    g.X64 = (double2*)x;
     g.cand = (PeakCand*)(g.X64 + spec * chunk);
+    g.ncand = n / row_block64(n);
     return;
   }
   g.T = (float2*)ws;
-  g.X = g.T + spec * chunk;
-  char* p = (char*)(g.X + spec * chunk);
-  g.Xb = nullptr;
-  g.Zc = nullptr;
-  if (split(ctx)) {
-    g.Xb = (unsigned*)p;
-    p += split_words(n) * sizeof(unsigned) * chunk;
-    g.Zc = (float2*)p;
-    p += (size_t)code_ny(n) * sizeof(float2) * chunk;
-  }
-  (void)p;
+  g.X = (float2*)x;
 }
 
 int check_image(ccpt_ctx* ctx, const void* data, int ny, int nx, int pitch, int dtype,
@@ -454,17 +461,6 @@ Marker marker_of(ccpt_ctx* ctx, hipStream_t s) {
   return m;
 }
 
-// Bytes of FP32 split-K partials a launch of `count` frames of size n uses
-// (0 when the launch is large enough to fill the GPU without splitting).
-size_t split_partials_bytes(const ccpt_ctx* ctx, int n, int count) {
-  if (ctx->o.precision != CCPT_PREC_FP32) return 0;
-  auto it = ctx->tables.find(table_key(n));
-  if (it == ctx->tables.end()) return 0;
-  const int mtiles = it->second.Mp / 32;
-  if ((long)count * mtiles >= split_blocks_for(ctx, n)) return 0;
-  return (size_t)count * mtiles * kSplitSlices * 32 * stage_b_k(code_nx(n)) * sizeof(float);
-}
-
 // With CCPT_FLAG_STREAMS the chunks of one group run on two streams (not
 // when launches are being timed, which needs them in sequence).
 bool use_slots(const ccpt_ctx* ctx) {
@@ -495,7 +491,7 @@ int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc,
   if (chunk < 1) return fail(ctx, CCPT_E_INVALID, "no workspace for one frame");
   SizeTables& t = ctx->tables[table_key(n)];
   const int ny = code_ny(n), nx = code_nx(n);
-  UpdftTables ut{t.ky, t.wb, t.Mp, ctx->o.precision, t.kfold};
+  const WindowTables wt{t.gy, t.gx, t.gxn, ctx->tf, ctx->td, t.ksteps, ctx->half};
   const Marker mark = mem.mark ? marker_of(ctx, s) : Marker{};
   // several chunks: alternate between the two slots (streams s and aux),
   // forked from and joined back into s
@@ -519,27 +515,15 @@ int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc,
     g.count = std::min(chunk, count - c0);
     g.out = out;
     carve(ctx, mem, n, chunk, slot, g);
-    // the one-kernel correlation leaves the split for the matrix DFT to make
-    if (g.Xb && xcorr_fused(ny, nx, pairs, g.count, g.fused_min)) g.Xb = nullptr;
-    if (g.Xb) g.Zc = nullptr;
-    const size_t yb = split_partials_bytes(ctx, n, g.count);
-    g.ypart = (yb && mem.ypart && yb <= mem.slot_ypart)
-                  ? (float*)((char*)mem.ypart + slot * mem.slot_ypart)
-                  : nullptr;
-    g.nparts = mem.nparts ? (double*)mem.nparts +
-                                (size_t)slot * kNewtonSplitMax * kNewtonParts * kNewtonCoef
-                          : nullptr;
+    const int parts = window_parts(ctx, n, g.count);
     if (mem.st_dirty) *mem.st_dirty = true;  // until this chunk's Newton launch has gone in
     if ((fp64(ctx) ? launch_xcorr64(n, g, cs, mark) : launch_xcorr(ny, nx, g, cs, mark)))
       return failed("correlation");
     mark(CCPT_STAGE_UPDFT, 1);
-    if ((fp64(ctx) ? launch_updft64(n, g, t.ky64, t.wb64, t.Mp, cs)
-                   : launch_updft(ny, nx, g, ut, cs)))
-      return failed("upsampled DFT");
+    if (launch_window_coef(ny, nx, g, wt, parts, cs)) return failed("window coefficient");
     mark(CCPT_STAGE_UPDFT, 0);
     mark(CCPT_STAGE_NEWTON, 1);
-    if (launch_newton(ny, nx, g, step_limit(ctx), cs))
-      return failed("Newton");
+    if (launch_window_max(ny, nx, g, wt, parts, step_limit(ctx), cs)) return failed("window maximum");
     mark(CCPT_STAGE_NEWTON, 0);
     if (mem.st_dirty) *mem.st_dirty = false;
   }
@@ -670,13 +654,6 @@ int ensure_state(ccpt_ctx* ctx, size_t count, hipStream_t s) {
     if (rc) return rc;
     ctx->st_dirty = true;
   }
-  if (!ctx->nparts) {
-    // one share per chunk slot (two) or lane (kMaxLanes)
-    const size_t bytes =
-        (size_t)kMaxLanes * kNewtonSplitMax * kNewtonParts * kNewtonCoef * sizeof(double);
-    int rc = ensure_buf(ctx, ctx->nparts, ctx->nparts_cap, bytes);
-    if (rc) return rc;
-  }
   if (ctx->st_dirty) {
     if (launch_init_state(ctx->st_buf, (int)ctx->st_cap, s))
       return fail(ctx, CCPT_E_HIP, "state initialisation launch failed");
@@ -687,7 +664,6 @@ int ensure_state(ccpt_ctx* ctx, size_t count, hipStream_t s) {
 
 // The streams and events of lanes 1.. (default priority).
 int create_lanes(ccpt_ctx* ctx) {
-  static_assert(kMaxLanes >= 2, "the two chunk slots use two Newton partial shares");
   for (int l = 0; l < kMaxLanes - 1; ++l)
     if (hipStreamCreateWithFlags(&ctx->lane_s[l], hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->lane_evt[l], hipEventDisableTiming) != hipSuccess)
@@ -762,6 +738,7 @@ int ccpt_create(ccpt_ctx** out, int device, const ccpt_options* opts) {
   ctx->o = o;
   ctx->M = M;
   ctx->c = M / 2;
+  ctx->half = window_half(0.5 * o.window, o.upsample, M, ctx->c);
   if (hipSetDevice(device) != hipSuccess || scratch_setup(device) != 0 ||
       hipEventCreateWithFlags(&ctx->desc_evt, hipEventDisableTiming) != hipSuccess ||
       hipEventCreateWithFlags(&ctx->fork_evt, hipEventDisableTiming) != hipSuccess ||
@@ -786,15 +763,9 @@ void ccpt_destroy(ccpt_ctx* ctx) {
     (void)hipEventDestroy(sp.b);
   }
   for (auto e : ctx->ev_pool) (void)hipEventDestroy(e);
-  for (auto& kv : ctx->tables) {
-    (void)hipFree(kv.second.tw);
-    (void)hipFree(kv.second.ky);
-    (void)hipFree(kv.second.wb);
-    if (kv.second.kfold) (void)hipFree(kv.second.kfold);
-    if (kv.second.tw64) (void)hipFree(kv.second.tw64);
-    if (kv.second.ky64) (void)hipFree(kv.second.ky64);
-    if (kv.second.wb64) (void)hipFree(kv.second.wb64);
-  }
+  for (auto& kv : ctx->tables) free_tables(kv.second);
+  if (ctx->tf) (void)hipFree(ctx->tf);
+  if (ctx->td) (void)hipFree(ctx->td);
   for (auto& r : ctx->refs) {
     (void)hipFree(r.spec);
     if (r.spec64) (void)hipFree(r.spec64);
@@ -815,9 +786,7 @@ void ccpt_destroy(ccpt_ctx* ctx) {
   if (ctx->small_evt) (void)hipEventDestroy(ctx->small_evt);
   if (ctx->gsmall) (void)hipFree(ctx->gsmall);
   if (ctx->acc_buf) (void)hipFree(ctx->acc_buf);
-  if (ctx->ypart) (void)hipFree(ctx->ypart);
   if (ctx->st_buf) (void)hipFree(ctx->st_buf);
-  if (ctx->nparts) (void)hipFree(ctx->nparts);
   if (ctx->rt_buf) (void)hipFree(ctx->rt_buf);
   if (ctx->h_small) (void)hipHostFree(ctx->h_small);
   delete ctx;
@@ -977,24 +946,20 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   }
   // per-lane needs (one lane: per chunk slot, two slots when some group has
   // several chunks and two-stream chunks are on)
-  std::vector<size_t> lws(nl, 0), lst(nl, 0), lyp(nl, 0);
+  std::vector<size_t> lws(nl, 0), lst(nl, 0);
   int nslots = 1;
   for (int gi = 0; gi < ngroups; ++gi) {
     const int nn = sig[2 * gi], cnt = sig[2 * gi + 1], l = lane_of[gi];
     const int chunk = std::min(cnt, chunk_for(ctx, nn));
     lws[l] = std::max(lws[l], frame_ws_bytes(nn, ctx->o.precision) * (size_t)chunk + 256);
     lst[l] = std::max(lst[l], (size_t)chunk);
-    lyp[l] = std::max(lyp[l], split_partials_bytes(ctx, nn, chunk));
-    lyp[l] = std::max(lyp[l], split_partials_bytes(ctx, nn, cnt % chunk));
     if (nl == 1 && cnt > chunk && use_slots(ctx)) nslots = 2;
   }
-  std::vector<size_t> ows(nl + 1, 0), ost(nl + 1, 0), oyp(nl + 1, 0);
+  std::vector<size_t> ows(nl + 1, 0), ost(nl + 1, 0);
   for (int l = 0; l < nl; ++l) {
     lws[l] = (lws[l] + 255) / 256 * 256;
-    lyp[l] = (lyp[l] + 255) / 256 * 256;
     ows[l + 1] = ows[l] + lws[l] * nslots;
     ost[l + 1] = ost[l] + lst[l] * nslots;
-    oyp[l + 1] = oyp[l] + lyp[l] * nslots;
   }
   rc = ensure_ws(ctx, ows[nl]);
   if (rc) return rc;
@@ -1002,12 +967,6 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   rc = ensure_state(ctx, ost[nl], s);
   if (rc) return rc;
   ctx->slot_st = lst[0];
-  if (oyp[nl] > ctx->ypart_cap) {
-    drop_graphs(ctx);
-    rc = ensure_buf(ctx, ctx->ypart, ctx->ypart_cap, oyp[nl]);
-    if (rc) return rc;
-  }
-  ctx->slot_ypart = lyp[0];
   rc = upload_desc(ctx, plan.desc, s);
   if (rc) return rc;
 
@@ -1026,11 +985,6 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
       mem.slot_ws = lws[l];
       mem.st = ctx->st_buf + ost[l];
       mem.slot_st = lst[l];
-      mem.ypart = ctx->ypart ? (char*)ctx->ypart + oyp[l] : nullptr;
-      mem.slot_ypart = lyp[l];
-      mem.nparts = ctx->nparts ? (double*)ctx->nparts +
-                                     (size_t)l * kNewtonSplitMax * kNewtonParts * kNewtonCoef
-                               : nullptr;
       if (nl > 1) mem.slots = false;
       hipStream_t ls = l ? ctx->lane_s[l - 1] : s;
       for (int gi = 0; gi < ngroups && r2 == CCPT_OK; ++gi) {
@@ -1499,12 +1453,11 @@ static void tune_shape(ccpt_ctx* ctx, int code, int count, const ccpt_roi* rois,
   };
   sweep_chunks();
   bool changed = false;
-  if (ctx->o.precision == CCPT_PREC_FP32)
-    for (int sb : {0, kSplitMaxBlocks, 512}) {
-      Schedule cand = sc;
-      cand.split_blocks = sb;
-      changed |= trial(cand);
-    }
+  for (int sb : {0, kSplitBlocks, 512}) {
+    Schedule cand = sc;
+    cand.split_blocks = sb;
+    changed |= trial(cand);
+  }
   if (code_ny(code) == 256 && code_nx(code) == 256 && !fp64(ctx))
     for (int fm : {1, kFusedMinFrames, 1 << 30}) {
       Schedule cand = sc;

@@ -22,18 +22,17 @@ struct FrameDesc {
 
 // Per-frame scratch passed between the kernels of one chunk.  It lives in a
 // buffer of its own that starts in the initial state (below) and is returned
-// to it by the Newton kernel, the last of a chunk, for every frame: no reset
+// to it by k_window_max, the last kernel of a chunk, for every frame: no reset
 // launch is needed per chunk.
 struct FrameState {
   unsigned long long peak_key;    // integer-lag maximum: value key << 32 | ~flat index
-  unsigned long long grid_key;    // upsampled-grid maximum, same encoding
+  unsigned long long grid_key;    // upsampled-grid maximum, same encoding (where the
+                                  // grid of a frame is spread over blocks)
   unsigned long long second_key;  // runner-up of the integer-lag correlation, same
                                   // encoding (0 until set; FP32 and split paths)
   unsigned amin, amax;            // order-preserving keys of min/max of A
   unsigned flags;                 // CCPT_ST_NONFINITE; CCPT_ST_NEAR_TIE (FP64 mode)
-  unsigned xmax;                  // largest |Re|, |Im| of the cross-power spectrum
-                                  // without its DC term, as float bits (the 256x256
-                                  // one-kernel correlation; 0 elsewhere)
+  unsigned done;                  // blocks of the frame whose grid share is in grid_key
 };
 
 // FP64 mode: best correlation value of one row block of a frame and its
@@ -57,12 +56,8 @@ struct GroupParams {
   int count;              // frames in the current chunk
   float2* T;              // workspace [count][N][N/2+1] (FFT intermediate)
   float2* X;              // workspace [count][N][N/2+1] (cross-power spectrum)
-  unsigned* Xb;           // split-precision copy of X for the matrix cores, or null:
-                          // [count][2 (hi, lo)][N/2][xb_pitch(N)] words, one word =
-                          // bf16 re | bf16 im << 16, ky contiguous, DC zeroed
-  float2* Zc;             // split precision on the one-kernel 256 x 256 path (Xb
-                          // null): [count][N], Z[ky] = X[ky, 0] + i X[ky, N/2] with
-                          // the DC term dropped; the matrix DFT splits X itself
+  double* coef;           // [count][parts][kChebN * kChebN] window coefficients (in
+                          // T's memory, which the correlation is done with by then)
   FrameState* st;         // [count]
   ccpt_result* out;       // caller's results
   const float2* tw;       // exp(-2 pi i m / N), m < N
@@ -73,16 +68,13 @@ struct GroupParams {
   int c;                  // grid centre index
   int newton_iters;
   double half_window;     // Newton results farther than this from p fall back
-  float* ypart;           // FP32 split-K partials for small launches, or null:
-                          // [count][Mp/32][slices][32][N rounded up to 32]
   // FP64 mode (all null otherwise): T and X in double2, the per-row-block
   // peak candidates [count][N / row_block64(N)], twiddles in FP64
-  double* nparts;         // Newton partial model coefficients of small launches, or
-                          // null: [count][kNewtonParts][kNewtonCoef] doubles
   double eps64;           // CC-SN offset (FP64 mode)
   double2* T64;
   double2* X64;
-  PeakCand* cand;
+  PeakCand* cand;         // [count][ncand]
+  int ncand;              // row blocks of a frame
   const double2* tw64;
   int pairs_ok;           // every frame is uint16 or float32 with an even pitch and
                           // pixel pairs aligned to their size (one load per pair)
@@ -105,21 +97,21 @@ struct GroupParams {
       X(216) X(256) X(288) X(324) X(384) X(432) X(486) X(512)
 #define CCPT_FOR_RECT(X) X(256, 128) X(512, 256) X(1024, 128)
 
-// Launches of fewer than kNewtonSplitMax frames build the first Newton model
-// over kNewtonParts blocks per frame (ky ranges), for latency.
-constexpr int kNewtonSplitMax = 64;
-constexpr int kNewtonParts = 8;
-constexpr int kNewtonCoef = 36;  // Taylor coefficients of the degree-7 model
+// Chebyshev terms per axis of the correlation on the window (refine.hip), and
+// the terms that the FP32 grid takes.
+constexpr int kChebN = 24;
+constexpr int kGridN = 16;
+constexpr int kMaxSide = 1024;  // longest side of a supported frame
+constexpr int kMaxCols = 512;   // longest row of a tall image
 
-// Small FP32 launches (fewer than kSplitMaxBlocks row tiles in all, the
-// default of the launch plan) split the Stage A contraction over kSplitSlices
-// ky slices for latency; the split happens where the launch set-up hands the
-// kernels a partials buffer (GroupParams::ypart).
-constexpr int kSplitMaxBlocks = 128;
-constexpr int kSplitSlices = 8;
+// Tiles of 16 spectrum columns (kx < NX/2) of a frame: the most blocks that
+// share one frame's coefficients.
+__host__ __device__ constexpr int window_tiles(int nx) { return (nx / 2 + 15) / 16; }
 
-// Row length (in words) of the split-precision spectrum rows: N rounded up to 32.
-__host__ __device__ constexpr int xb_pitch(int n) { return (n + 31) / 32 * 32; }
+// Launch plan default (ccpt_plan.split_blocks): launches of fewer than this
+// many frames spread a frame's coefficient pass over several blocks
+// (window_parts in api.cpp).
+constexpr int kSplitBlocks = 128;
 
 // Rows per block of the FP64 row passes: 8 rows when they fit, else the
 // largest divisor of N whose rows hold at most 1024 complex values.
@@ -222,7 +214,7 @@ int launch_spectrum(int ny, int nx, const void* data, int dtype, int pitch, long
 
 // The correlation stage of 256 x 256 frames (FP32 and split precision) in
 // one kernel with the half spectrum held in registers: the same outputs as
-// the three passes of launch_xcorr (X, Xb, the frame states), no T.
+// the three passes of launch_xcorr (X, the frame states), no T.
 int launch_xcorr256(const GroupParams& g, hipStream_t s);
 
 // Whether a launch of `count` frames of ny x nx takes that one-kernel path
@@ -244,39 +236,27 @@ int launch_spectrum64(int N, const void* data, int dtype, int pitch, long img_st
                       int weight, double eps, int conj_out, double2* T, double2* spec,
                       const double2* tw, hipStream_t s);
 
-// Stage 4: upsampled matrix DFT around the integer peak and its maximum.
-struct UpdftTables {
-  const void* ky;    // Stage A operand table (layout depends on precision)
-  const void* wb;    // Stage B operand table
-  int Mp;            // padded grid size (multiple of 32)
-  int precision;
-  const void* kfold; // split precision, NX >= 256: folded K' table for every peak row
+// Tables of the window expansion (tables.h builds them): per shape gy, gx,
+// gxn and ksteps, per context tf, td and half.
+struct WindowTables {
+  const double2* gy;  // [ksteps][64]: row-pair weights of even and odd n
+  const double2* gx;  // [tiles][4][64]: column weights of even and odd m
+  const double* gxn;  // [kChebN / 2]: Nyquist column, even m
+  const float* tf;    // [M rounded to 32][kGridN]: T_n at the grid offsets
+  const double* td;   // [M rounded to 16][kChebN]: the same in FP64
+  int ksteps;         // k steps of 4 row pairs
+  double half;        // B: the series holds for |e| <= half px
 };
 
-// Minimum row length NX of the wide split-precision kernel (and its folded table).
-constexpr int kWideMinN = 256;
-// 32-row grid tiles per block of the wide kernel.
-constexpr int kWideMT = 5;
+// Stage 4: the window coefficients of each frame from its spectrum (g.X64
+// when set, else g.X), summed by `nparts` blocks per frame into g.coef.
+int launch_window_coef(int ny, int nx, const GroupParams& g, const WindowTables& t, int nparts,
+                       hipStream_t s);
 
-// Rows per plane of the folded table: Mp padded to whole blocks of kWideMT
-// tiles (zero rows), so every block of the wide kernel runs all its tiles.
-__host__ __device__ constexpr int kfold_rows(int Mp) {
-  return (Mp / 32 + kWideMT - 1) / kWideMT * kWideMT * 32;
-}
-
-// Builds the folded split table [NY][2][rows][xb_pitch(NY)] words on the
-// device for frames of NY rows (rows = kfold_rows(Mp); rows m >= M are zero).
-int launch_build_kfold(unsigned* out, int N, int u, int M, int c, int rows, int f16, hipStream_t s);
-int launch_updft(int ny, int nx, const GroupParams& g, const UpdftTables& t, hipStream_t s);
-
-// FP64 mode: reduces the peak candidates, then the upsampled DFT in FP64 on
-// the vector units; K [Mp][N] and W [N/2+1][Mp] are complex FP64 tables.
-int launch_updft64(int N, const GroupParams& g, const double2* K, const double2* W, int Mp,
-                   hipStream_t s);
-
-// Stage 5: FP64 Newton refinement and the result record (from g.X64 when
-// set, else from g.X).
-int launch_newton(int ny, int nx, const GroupParams& g, double step_limit, hipStream_t s);
+// Stage 5: the upsampled grid's maximum, the FP64 Newton refinement and the
+// result record.
+int launch_window_max(int ny, int nx, const GroupParams& g, const WindowTables& t, int nparts,
+                      double step_limit, hipStream_t s);
 
 // Inverse 2-D c2r of n half spectra [n][ny][nx/2+1] into n float images of
 // ny rows of nx (the tall layout of a rectangle) scaled by `scale` (T is

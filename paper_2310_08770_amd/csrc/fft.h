@@ -53,58 +53,6 @@ __device__ __forceinline__ C mul_i(C a) {
   return SIGN > 0 ? mkc<C>(-a.y, a.x) : mkc<C>(a.y, -a.x);
 }
 
-// bf16 (round to nearest even) of a float, as the high 16 bits of its pattern
-__device__ __forceinline__ unsigned bf16_bits(float f) {
-  unsigned b = __float_as_uint(f);
-  b += 0x7FFFu + ((b >> 16) & 1u);
-  return b >> 16;
-}
-__device__ __forceinline__ float bf16_float(unsigned h) { return __uint_as_float(h << 16); }
-
-typedef __bf16 bf16x2_v __attribute__((ext_vector_type(2)));
-typedef float f32x2_v __attribute__((ext_vector_type(2)));
-
-// bf16 (round to nearest even) of two floats, packed a | b << 16: the same
-// bits as bf16_bits for finite values, in one conversion instruction
-__device__ __forceinline__ unsigned bf16_pack(float a, float b) {
-  const f32x2_v v = {a, b};
-  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2_v));
-}
-// the low and high halves of a packed pair as floats
-__device__ __forceinline__ float bf16_lo_float(unsigned w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16_hi_float(unsigned w) { return __uint_as_float(w & 0xFFFF0000u); }
-
-// bf16 hi + lo split of two floats (x ~ hi + lo to about 16 significant
-// bits), each packed as a | b << 16.
-__device__ __forceinline__ void split2(float a, float b, unsigned& hi, unsigned& lo) {
-  hi = bf16_pack(a, b);
-  lo = bf16_pack(a - bf16_lo_float(hi), b - bf16_hi_float(hi));
-}
-
-// Splits a complex value into bf16 hi + lo words (re in the low half, im in
-// the high half of each word): v ~ hi + lo to about 16 significant bits.
-__device__ __forceinline__ void split_pair(float2 v, unsigned& hi, unsigned& lo) {
-  split2(v.x, v.y, hi, lo);
-}
-
-// fp16 hi + lo split of two floats (x ~ hi + lo to about 22 significant bits
-// while |x| stays inside the fp16 range), each packed as a | b << 16.
-__device__ __forceinline__ unsigned f16_pack(float a, float b) {
-  const _Float16 ha = (_Float16)a, hb = (_Float16)b;
-  return (unsigned)__builtin_bit_cast(unsigned short, ha) |
-         ((unsigned)__builtin_bit_cast(unsigned short, hb) << 16);
-}
-__device__ __forceinline__ float f16_lo_float(unsigned w) {
-  return (float)__builtin_bit_cast(_Float16, (unsigned short)(w & 0xFFFFu));
-}
-__device__ __forceinline__ float f16_hi_float(unsigned w) {
-  return (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16));
-}
-__device__ __forceinline__ void split2_f16(float a, float b, unsigned& hi, unsigned& lo) {
-  hi = f16_pack(a, b);
-  lo = f16_pack(a - f16_lo_float(hi), b - f16_hi_float(hi));
-}
-
 // LDS layout of an FFT sequence: element i sits at lds_idx(i), with one
 // unused slot after every 2^kLdsPadShift elements when the shift is nonzero,
 // so the strided writes of the early Stockham stages spread over the LDS

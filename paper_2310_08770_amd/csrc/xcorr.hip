@@ -122,7 +122,7 @@ __global__ void k_init_state(FrameState* st, int count) {
     s.amin = 0xFFFFFFFFu;
     s.amax = 0;
     s.flags = 0;
-    s.xmax = 0;
+    s.done = 0;
     st[i] = s;
   }
 }
@@ -242,9 +242,7 @@ enum ColKind { COL_XCORR = 0, COL_FWD = 1, COL_FWD_CONJ = 2, COL_INV = 3 };
 
 // Column pass over the NX/2+1 columns of length NY: block b takes columns
 // b*CB .. b*CB+CB-1 of the first NX/2, and block 0 also takes the Nyquist
-// column NX/2 (so no
-// block is left with a single column, and block 0 holds both real-output
-// columns 0 and N/2 for the packed split-precision copy).
+// column NX/2 (so no block is left with a single column).
 //  COL_XCORR:    forward FFT, X = F[A] * rspec (stored to X), inverse FFT back into T
 //  COL_FWD:      forward FFT stored to `spec`
 //  COL_FWD_CONJ: conjugate of the forward FFT stored to `spec`
@@ -252,7 +250,6 @@ enum ColKind { COL_XCORR = 0, COL_FWD = 1, COL_FWD_CONJ = 2, COL_INV = 3 };
 template <int NY, int NX, int CB, int KIND, typename C>
 __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__ desc, int first,
                                                    C* __restrict__ T, C* __restrict__ X,
-                                                   unsigned* __restrict__ Xb,
                                                    C* __restrict__ spec, long spec_stride,
                                                    const C* __restrict__ gtw) {
   constexpr int H = NX / 2 + 1, S = lds_len(NY) + 1, NC = NX / 2;
@@ -322,35 +319,6 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
         }
       }
       __syncthreads();
-      if constexpr (sizeof(C) == sizeof(float2)) {
-      if (Xb) {
-        // bf16 hi/lo split of X for the matrix cores: one row per column
-        // kx < NX/2, ky contiguous, rows padded to xb_pitch(NY) with zeros.
-        // Row 0 carries Z = X[., 0] + i X[., NX/2]: both columns give real
-        // Stage A outputs, so Re and Im of the product with Z are the two of
-        // them.  The DC term X[0, 0] is dropped.
-        constexpr int P = xb_pitch(NY);
-        unsigned* hi = Xb + (size_t)f * 2 * NC * P;
-        unsigned* lo = hi + (size_t)NC * P;
-        for (int i = tid; i < nreg * P; i += kThreads) {
-          const int c = i / P, y = i - c * P;
-          const int kx = c0 + c;
-          float2 v = make_float2(0.f, 0.f);
-          if (y < NY) {
-            v = r[c * S + lds_idx(y)];
-            if (kx == 0) {
-              if (y == 0) v.x = 0.f;
-              const float2 nq = r[CB * S + lds_idx(y)];
-              v = make_float2(v.x - nq.y, v.y + nq.x);  // + i * X[y, N/2]
-            }
-          }
-          unsigned wh, wl;
-          split_pair(v, wh, wl);
-          hi[(size_t)kx * P + y] = wh;
-          lo[(size_t)kx * P + y] = wl;
-        }
-      }
-      }
       C* o = (r == bufA) ? bufB : bufA;
       C* q = fft_lds<NY, +1, NY>(r, o, nseq, S, tw);
       for (int i = tid; i < NY * nseq; i += kThreads) {
@@ -521,8 +489,7 @@ static int xcorr_n(const GroupParams& g, hipStream_t s, const Marker& mark) {
   mark(CCPT_STAGE_ROWS_FWD, 0);
   mark(CCPT_STAGE_COLS, 1);
   hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_XCORR, float2>), dim3((NX / 2 + CB - 1) / CB, g.count),
-                     dim3(kThreads), 0, s, g.desc, g.first, g.T, g.X, g.Xb, (float2*)nullptr, 0L,
-                     g.tw);
+                     dim3(kThreads), 0, s, g.desc, g.first, g.T, g.X, (float2*)nullptr, 0L, g.tw);
   mark(CCPT_STAGE_COLS, 0);
   mark(CCPT_STAGE_ROWS_INV, 1);
   hipLaunchKernelGGL((k_rows_inv<NY, NX, RPB, true, float2>), dim3(NY / RPB, g.count),
@@ -543,8 +510,8 @@ static int xcorr64_n(const GroupParams& g, hipStream_t s, const Marker& mark) {
   mark(CCPT_STAGE_ROWS_FWD, 0);
   mark(CCPT_STAGE_COLS, 1);
   hipLaunchKernelGGL((k_cols<N, N, CB, COL_XCORR, double2>), dim3((N / 2 + CB - 1) / CB, g.count),
-                     dim3(kThreads), 0, s, g.desc, g.first, g.T64, g.X64, (unsigned*)nullptr,
-                     (double2*)nullptr, 0L, g.tw64);
+                     dim3(kThreads), 0, s, g.desc, g.first, g.T64, g.X64, (double2*)nullptr,
+                     0L, g.tw64);
   mark(CCPT_STAGE_COLS, 0);
   mark(CCPT_STAGE_ROWS_INV, 1);
   hipLaunchKernelGGL((k_rows_inv<N, N, RPB, true, double2>), dim3(N / RPB, g.count),
@@ -565,12 +532,10 @@ static int spectrum_n(const void* data, int dtype, int pitch, long img_stride, i
                      weight, eps, T, (FrameState*)nullptr, tw);
   if (conj_out)
     hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_FWD_CONJ, C>), dim3((NX / 2 + CB - 1) / CB, n),
-                       dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (C*)nullptr,
-                       (unsigned*)nullptr, spec, (long)NY * H, tw);
+                       dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (C*)nullptr, spec, (long)NY * H, tw);
   else
     hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_FWD, C>), dim3((NX / 2 + CB - 1) / CB, n),
-                       dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (C*)nullptr,
-                       (unsigned*)nullptr, spec, (long)NY * H, tw);
+                       dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (C*)nullptr, spec, (long)NY * H, tw);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -587,8 +552,7 @@ static int frame_spectra_n(const FrameDesc* desc, int first, int count, int mode
                      s, src, mode == CCPT_MODE_CCSN ? 2 : 0, (double)eps, T, (FrameState*)nullptr,
                      tw);
   hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_FWD, float2>), dim3((NX / 2 + CB - 1) / CB, count),
-                     dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (float2*)nullptr,
-                     (unsigned*)nullptr, spec, (long)NY * H, tw);
+                     dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (float2*)nullptr, spec, (long)NY * H, tw);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -601,7 +565,7 @@ static int inverse_n(const float2* spec, int n, float scale, float2* T, float* i
   constexpr int H = NX / 2 + 1;
   hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_INV, float2>), dim3((NX / 2 + CB - 1) / CB, n),
                      dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (float2*)nullptr,
-                     (unsigned*)nullptr, (float2*)spec, (long)NY * H, tw);
+                     (float2*)spec, (long)NY * H, tw);
   hipLaunchKernelGGL((k_rows_inv<NY, NX, RPB, false, float2>), dim3(NY / RPB, n), dim3(kThreads), 0,
                      s, T, (FrameState*)nullptr, img, scale, tw, (PeakCand*)nullptr, 0);
   return hipGetLastError() == hipSuccess ? 0 : -1;

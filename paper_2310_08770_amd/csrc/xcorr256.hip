@@ -10,7 +10,7 @@
 // 256 = 16 x 16), and between stages the values move through LDS in two
 // rounds of 128 KB (a frame's half spectrum is 256 KB, LDS 160 KB).  Nothing
 // but the frame, the reference spectrum (shared, L2-resident) and the
-// outputs X (and its split copy) touches memory.
+// output X touches memory.
 //
 // Index conventions (t = thread, all per row y or column kx of the frame):
 //   z[y][n] = A[y][2n] + i A[y][2n+1], n < 128; Z = FFT128(z) along n.
@@ -156,17 +156,15 @@ __device__ __forceinline__ T wave_max(T v) {
 
 }  // namespace
 
-template <bool SPLIT, bool SN>
+template <bool SN>
 __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   __shared__ __align__(16) float2 lds[kLds];
   __shared__ float2 tw[N];
   __shared__ float2 stage[2 * N];  // products of the real columns 0 and N/2
   __shared__ float redf[2][kT / 64];
   __shared__ unsigned redu[4][kT / 64];
-  __shared__ unsigned xmax_s;  // split precision: largest |Re|, |Im| of X without DC (float bits)
   const int t = threadIdx.x;
   const int f = blockIdx.x;
-  if (t == 0) xmax_s = 0u;
   const FrameDesc desc = g.desc[g.first + f];
   for (int i = t; i < N; i += kT) tw[i] = g.tw[i];
 
@@ -395,16 +393,6 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
       }
       const int col = cp + 64 * i;
       const bool packed = i == 0 && cp == 0;
-      // split precision: the largest |Re|, |Im| of the X values this thread
-      // stores, merged into xmax_s right after the stores (non-negative floats
-      // order as their bits), so no register carries it further
-      float xmx = 0.f;
-      auto merge_xmax = [&]() {
-        if constexpr (SPLIT) {
-          const unsigned xw = wave_max(__float_as_uint(xmx));
-          if ((t & 63) == 0) atomicMax(&xmax_s, xw);
-        }
-      };
       if (packed) {
         // P = F0 + i F128 with F0, F128 the spectra of the real columns 0 and
         // N/2: F0[ky] = (P[ky] + conj P[-ky]) / 2, F128 = (P[ky] - conj P[-ky]) / 2i;
@@ -491,28 +479,13 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
           const int ky = kap(hp, e >> 4) + 16 * (e & 15);
           const float2 x = r[pslot(e, i)];
           Xf[(size_t)ky * H + col] = x;
-          if constexpr (SPLIT) xmx = fmaxf(xmx, fmaxf(fabsf(x.x), fabsf(x.y)));
         }
       }
-      merge_xmax();
       if (i == 0) {
-        // the two real columns' products, staged by the packed lanes; in
-        // split precision also Z = X[., 0] + i X[., N/2] without the DC term,
-        // the packed column the matrix DFT takes as its kx = 0 operand
+        // the two real columns' products, staged by the packed lanes
         __syncthreads();
-        for (int e = t; e < 2 * N; e += kT) {
-          const float2 x = stage[e];
-          Xf[(size_t)(e & (N - 1)) * H + (e >> 8) * (N / 2)] = x;
-          if constexpr (SPLIT)
-            if (e) xmx = fmaxf(xmx, fmaxf(fabsf(x.x), fabsf(x.y)));  // (e = 0: the DC term)
-        }
-        merge_xmax();
-        if constexpr (SPLIT) {
-          for (int ky = t; ky < N; ky += kT) {
-            const float2 x0 = stage[ky], x1 = stage[N + ky];
-            g.Zc[(size_t)f * N + ky] = make_float2((ky ? x0.x : 0.f) - x1.y, x0.y + x1.x);
-          }
-        }
+        for (int e = t; e < 2 * N; e += kT)
+          Xf[(size_t)(e & (N - 1)) * H + (e >> 8) * (N / 2)] = stage[e];
       }
       // I1: inverse DFT over d, twiddle W256^{-c a'}
 #pragma unroll
@@ -740,7 +713,6 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
       bad |= redu[2][w];
     }
     FrameState& st = g.st[f];
-    st.xmax = SPLIT ? xmax_s : 0u;
     st.peak_key = peak_key(t1, idx);
     st.second_key = peak_key(t2, 0u);
     st.amin = kmin;
@@ -751,14 +723,10 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
 
 int launch_xcorr256(const GroupParams& g, hipStream_t s) {
   const bool sn = g.mode == CCPT_MODE_CCSN;
-  if (g.Zc && sn)
-    hipLaunchKernelGGL((k_xcorr256<true, true>), dim3(g.count), dim3(kT), 0, s, g);
-  else if (g.Zc)
-    hipLaunchKernelGGL((k_xcorr256<true, false>), dim3(g.count), dim3(kT), 0, s, g);
-  else if (sn)
-    hipLaunchKernelGGL((k_xcorr256<false, true>), dim3(g.count), dim3(kT), 0, s, g);
+  if (sn)
+    hipLaunchKernelGGL((k_xcorr256<true>), dim3(g.count), dim3(kT), 0, s, g);
   else
-    hipLaunchKernelGGL((k_xcorr256<false, false>), dim3(g.count), dim3(kT), 0, s, g);
+    hipLaunchKernelGGL((k_xcorr256<false>), dim3(g.count), dim3(kT), 0, s, g);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -285,11 +285,36 @@ struct Deriv {
   double c, gy, gx, hyy, hxy, hxx;
 };
 
-// Sums over the 64 lanes of a wave (every lane receives them), fixed order.
+// Lane moves of doubles by DPP (operand modifiers of VALU moves: no LDS
+// traffic).  Every lane of the wave is active in the callers; lanes outside
+// ROWS (or without a source lane) receive 0.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, CTRL, ROWS, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), CTRL, ROWS, 0xF, true);
+  return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+// A lane's value for the whole wave, in scalar registers.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Sum over the 64 lanes of a wave, fixed order: quads, half rows and rows of
+// 16 by quad permutations and mirrors, then rows into the next (row_bcast),
+// the total in lane 63.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_f64<0xB1>(v);        // quad [1, 0, 3, 2]
+  v += dpp_f64<0x4E>(v);        // quad [2, 3, 0, 1]
+  v += dpp_f64<0x141>(v);       // half-row mirror
+  v += dpp_f64<0x140>(v);       // row mirror
+  v += dpp_f64<0x142, 0xA>(v);  // lane 15 of each row to the next: rows 1 and 3
+  v += dpp_f64<0x143, 0xC>(v);  // lane 31 to rows 2 and 3
+  return lane_value(v, 63);
 }
 
 // C and its first and second derivatives (per px) at offset (ey, ex) from the
@@ -464,7 +489,6 @@ __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 
   constexpr bool FP64 = sizeof(CX) != sizeof(float2);
   constexpr int NW = kMThreads / 64;
   __shared__ double c[kNC2];
-  __shared__ __align__(16) float cf[kGridN * kGridN];
   __shared__ double redd[NW][6];
   __shared__ unsigned long long redk[NW];
   __shared__ unsigned redi[NW];
@@ -475,6 +499,28 @@ __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 
   const int f = blockIdx.y, part = blockIdx.x;
   const FrameState st = g.st[f];
   const FrameDesc d = g.desc[g.first + f];
+  // the coefficients are requested with the state (a skipped frame's are
+  // whatever the buffer holds, and unused), the parts in groups of up to
+  // eight at a time, added in order
+  constexpr int kPer = (kNC2 + kMThreads - 1) / kMThreads;
+  double cv[kPer];
+  {
+    const double* src = g.coef + (size_t)f * nparts * kNC2;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) cv[e] = src[min(tid + e * kMThreads, kNC2 - 1)];
+    for (int p0 = 1; p0 < nparts; p0 += 8) {
+      double a[8][kPer];
+#pragma unroll
+      for (int p = 0; p < 8; ++p)
+#pragma unroll
+        for (int e = 0; e < kPer; ++e)
+          a[p][e] = src[(size_t)min(p0 + p, nparts - 1) * kNC2 + min(tid + e * kMThreads, kNC2 - 1)];
+#pragma unroll
+      for (int p = 0; p < 8; ++p)
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) cv[e] += p0 + p < nparts ? a[p][e] : 0.0;
+    }
+  }
   ccpt_result* out = g.out + d.out_idx;
   const int M = g.M;
   const bool tr = ny != nx && g.trans;
@@ -490,83 +536,107 @@ __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 
     }
     return;
   }
-  // ---- coefficients, the parts in order
-  {
-    const double* src = g.coef + (size_t)f * nparts * kNC2;
-    for (int i = tid; i < kNC2; i += kMThreads) {
-      double v = src[i];
-      for (int p = 1; p < nparts; ++p) v += src[(size_t)p * kNC2 + i];
-      c[i] = v;
-    }
-    if constexpr (FP64) {
-      if (tid == 0) {
-        bool tie;
-        cpk[0] = peak_of_cands(g.cand + (size_t)f * g.ncand, g.ncand, tie);
-        cpk[1] = tie ? CCPT_ST_NEAR_TIE : 0u;
-      }
+  // ---- coefficients into LDS, the parts in order
+#pragma unroll
+  for (int e = 0; e < kPer; ++e) {
+    const int i = tid + e * kMThreads;
+    if (i < kNC2) c[i] = cv[e];
+  }
+  if constexpr (FP64) {
+    if (tid == 0) {
+      bool tie;
+      cpk[0] = peak_of_cands(g.cand + (size_t)f * g.ncand, g.ncand, tie);
+      cpk[1] = tie ? CCPT_ST_NEAR_TIE : 0u;
     }
   }
   __syncthreads();
   unsigned best_idx;
   if constexpr (!FP64) {
-    // ---- scale: the largest coefficient but the constant to [0.5, 1)
-    double mx = 0.0;
-    for (int i = tid; i < kNC2; i += kMThreads) mx = fmax(mx, i ? fabs(c[i]) : 0.0);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, 64));
-    if (lane == 0) redd[wave][0] = mx;
-    __syncthreads();
-    mx = redd[0][0];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) mx = fmax(mx, redd[w][0]);
-    int ex = 0;
-    if (mx > 0.0 && mx < __builtin_inf()) (void)frexp(mx, &ex);
-    for (int i = tid; i < kGridN * kGridN; i += kMThreads) {
-      const int n = i / kGridN, m = i - n * kGridN;
-      cf[i] = i ? (float)ldexp(c[n * kChebN + m], -ex) : 0.f;
-    }
-    __syncthreads();
-    // ---- strips of 32 grid columns
     const int l32 = lane & 31, h = lane >> 5;
-    const int nt = (M + 31) / 32;
-    unsigned long long best = 0;
-    // A operand of V: row n of c (rows 16.. of the 32-row product are zero)
+    // ---- scale: the largest coefficient but the constant to [0.5, 1) (every
+    // wave finds it for itself)
     float4 c0 = make_float4(0.f, 0.f, 0.f, 0.f), c1 = c0;
-    if (l32 < kGridN) {
-      c0 = *(const float4*)(cf + l32 * kGridN + 4 * h);
-      c1 = *(const float4*)(cf + l32 * kGridN + 8 + 4 * h);
-    }
-    for (int s = part * NW + wave; s < nt; s += nb * NW) {
-      const int mx0 = s * 32 + l32;
-      // k step j of both products takes terms term(j, h) = 8 (j / 4) + 4 h + j
-      // mod 4, which is the row that register j of a 32x32 product holds in
-      // lane half h: V comes out of the first product as the second's B operand
-      f32x16 vb;
-      {
-        const float4 t0 = *(const float4*)(t.tf + (size_t)mx0 * kGridN + 4 * h);
-        const float4 t1 = *(const float4*)(t.tf + (size_t)mx0 * kGridN + 8 + 4 * h);
-        vb = grid_mma(c0, c1, t0, t1);
+    {
+      double big = 0.0;
+#pragma unroll
+      for (int e = 0; e < kNC2 / 64; ++e) {
+        const int i = lane + 64 * e;
+        big = fmax(big, i ? fabs(c[i]) : 0.0);
       }
-      float bv = -__builtin_inff();
-      int br = 0;
-      for (int r = 0; r < nt; ++r) {
-        const float4 t0 = *(const float4*)(t.tf + (size_t)(r * 32 + l32) * kGridN + 4 * h);
-        const float4 t1 = *(const float4*)(t.tf + (size_t)(r * 32 + l32) * kGridN + 8 + 4 * h);
-        const f32x16 u = grid_mma(t0, t1, make_float4(vb[0], vb[1], vb[2], vb[3]),
-                                  make_float4(vb[4], vb[5], vb[6], vb[7]));
-        // rows in increasing order within a lane: a strict compare keeps the
-        // lowest of equal values, in either orientation of the frame
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+      int ex = 0;
+      if (big > 0.0 && big < __builtin_inf()) (void)frexp(big, &ex);
+      // A operand of V: row n of c (rows 16.. of the 32-row product are zero)
+      if (l32 < kGridN) {
+        const double* r = c + l32 * kChebN + 4 * h;
+        c0 = make_float4((float)ldexp(r[0], -ex), (float)ldexp(r[1], -ex), (float)ldexp(r[2], -ex),
+                         (float)ldexp(r[3], -ex));
+        c1 = make_float4((float)ldexp(r[8], -ex), (float)ldexp(r[9], -ex), (float)ldexp(r[10], -ex),
+                         (float)ldexp(r[11], -ex));
+        if (lane == 0) c0.x = 0.f;  // the constant
+      }
+    }
+    // ---- 32 x 32 tiles of the grid, column strip by column strip; each wave
+    // of the frame's blocks takes an equal run of them
+    const int nt = (M + 31) / 32;
+    const int nw = nb * NW, w0 = part * NW + wave;
+    const int k1 = (int)((long)(w0 + 1) * nt * nt / nw);
+    unsigned long long best = 0;
+    float bv = -__builtin_inff();
+    int br = 0;
+    f32x16 vb;
+    int k = (int)((long)w0 * nt * nt / nw), s = k / nt, r = k - s * nt;
+    bool fresh = true;  // the strip's V is due
+    // k step j of both products takes terms 8 (j / 4) + 4 h + j mod 4, which
+    // is the row that register j of a 32x32 product holds in lane half h: V
+    // comes out of the first product as the second's B operand
+    const float* ta = t.tf + (size_t)l32 * kGridN + 4 * h;
+    float4 t0, t1;  // A operand of the next tile: T(y) of rows 32 r + lane mod 32
+    if (k < k1) {
+      t0 = *(const float4*)(ta + (size_t)r * 32 * kGridN);
+      t1 = *(const float4*)(ta + (size_t)r * 32 * kGridN + 8);
+    }
+    for (; k < k1; ++k) {
+      if (fresh) {
+        const float4 x0 = *(const float4*)(ta + (size_t)s * 32 * kGridN);
+        const float4 x1 = *(const float4*)(ta + (size_t)s * 32 * kGridN + 8);
+        vb = grid_mma(c0, c1, x0, x1);
+        fresh = false;
+      }
+      const f32x16 u = grid_mma(t0, t1, make_float4(vb[0], vb[1], vb[2], vb[3]),
+                                make_float4(vb[4], vb[5], vb[6], vb[7]));
+      const int row0 = r * 32 + 4 * h, mx0 = s * 32 + l32;
+      const bool whole = r * 32 + 32 <= M;
+      if (++r == nt) {
+        r = 0;
+        ++s;
+        fresh = true;
+      }
+      t0 = *(const float4*)(ta + (size_t)r * 32 * kGridN);
+      t1 = *(const float4*)(ta + (size_t)r * 32 * kGridN + 8);
+      // rows in increasing order within a lane: a strict compare keeps the
+      // lowest of equal values, in either orientation of the frame
+      if (whole) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const int my = r * 32 + (v >> 2) * 8 + 4 * h + (v & 3);
+          const bool gt = u[v] > bv;
+          bv = gt ? u[v] : bv;
+          br = gt ? row0 + (v >> 2) * 8 + (v & 3) : br;
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int my = row0 + (v >> 2) * 8 + (v & 3);
           const bool gt = u[v] > bv && my < M;
           bv = gt ? u[v] : bv;
           br = gt ? my : br;
         }
       }
-      if (mx0 < M && bv > -__builtin_inff()) {
+      if (fresh || k + 1 == k1) {  // the lane's column is done
         const unsigned long long key = peak_key(bv, grid_index(br, mx0, M, tr));
-        best = key > best ? key : best;
+        if (mx0 < M && bv > -__builtin_inff()) best = key > best ? key : best;
+        bv = -__builtin_inff();
       }
     }
 #pragma unroll
@@ -800,10 +870,11 @@ int launch_window_coef(int ny, int nx, const GroupParams& g, const WindowTables&
 
 int launch_window_max(int ny, int nx, const GroupParams& g, const WindowTables& t, int nparts,
                       double step_limit, hipStream_t s) {
-  // few frames: a frame's grid is spread over blocks of four strips each
+  // few frames: a frame's grid is spread over blocks (three tiles a wave) as
+  // long as there are CUs without one
   const int strips = (g.M + 31) / 32;
   int nb = 1;
-  if (!g.X64) nb = std::max(1, std::min((strips + 3) / 4, 512 / std::max(1, g.count)));
+  if (!g.X64) nb = std::max(1, std::min((strips * strips + 11) / 12, 256 / std::max(1, g.count)));
   if (g.X64)
     hipLaunchKernelGGL((k_window_max<double2>), dim3(1, g.count), dim3(kMThreads), 0, s, g, t, ny, nx, nparts, 1,
                        step_limit);

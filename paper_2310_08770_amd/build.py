@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libccpt.so")
 OBJDIR = os.path.join(HERE, "_build")
 
-SOURCES = ["api.cpp", "xcorr.hip", "xcorr256.hip", "refine.hip", "grad.hip", "reference.hip",
+SOURCES = ["api.cpp", "xcorr.hip", "xcorr256.hip", "xcorr_lds.hip", "refine.hip", "grad.hip", "reference.hip",
            "scratch.hip"]
 
 FLAGS = [

@@ -229,6 +229,21 @@ inline bool xcorr_fused(int ny, int nx, bool pairs_ok, int count, int fused_min)
   return ny == 256 && nx == 256 && pairs_ok && count >= fused_min;
 }
 
+// The correlation stage of frames whose half spectrum fits LDS in one kernel,
+// one block per frame (xcorr_lds.hip): the same bits as the three passes.
+// xcorr_lds_frames: how many of a launch's `count` frames, from the first,
+// take it.  Frames of at most kLdsSmall half-spectrum values (128 x 128) always
+// do: several blocks share a CU, and even one frame alone is no slower than
+// three launches.  Larger ones have a CU each, so they go in rounds of
+// kLdsRound (the chip's CUs); a last round of under kLdsMinFrames frames is
+// left to the three passes, which spread a frame over many CUs (192 x 192: a
+// round takes 57 us, the passes 40 us for 64 frames and 60 us for 128).
+constexpr int kLdsSmall = 8320;
+constexpr int kLdsRound = 256;
+constexpr int kLdsMinFrames = 128;
+int xcorr_lds_frames(int ny, int nx, int count);
+int launch_xcorr_lds(int ny, int nx, const GroupParams& g, hipStream_t s);
+
 // FP64 mode: the same two calls with every FFT in FP64 (g.T64, g.X64,
 // g.cand; the integer peak is left as per-row-block candidates).
 int launch_xcorr64(int N, const GroupParams& g, hipStream_t s, const Marker& mark);

@@ -571,13 +571,29 @@ static int inverse_n(const float2* spec, int n, float scale, float2* T, float* i
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_xcorr(int ny, int nx, const GroupParams& g, hipStream_t s, const Marker& mark) {
-  if (xcorr_fused(ny, nx, g.pairs_ok != 0, g.count, g.fused_min)) {
+int launch_xcorr(int ny, int nx, const GroupParams& g0, hipStream_t s, const Marker& mark) {
+  if (xcorr_fused(ny, nx, g0.pairs_ok != 0, g0.count, g0.fused_min)) {
     mark(CCPT_STAGE_XCORR, 1);
-    const int rc = launch_xcorr256(g, s);
+    const int rc = launch_xcorr256(g0, s);
     mark(CCPT_STAGE_XCORR, 0);
     return rc;
   }
+  const int nl = xcorr_lds_frames(ny, nx, g0.count);
+  if (nl > 0) {
+    GroupParams a = g0;
+    a.count = nl;
+    mark(CCPT_STAGE_XCORR, 1);
+    const int rc = launch_xcorr_lds(ny, nx, a, s);
+    mark(CCPT_STAGE_XCORR, 0);
+    if (rc || nl == g0.count) return rc;
+  }
+  GroupParams g = g0;  // the frames that are left
+  const size_t spec = (size_t)ny * (nx / 2 + 1);
+  g.first += nl;
+  g.count -= nl;
+  g.T += spec * nl;
+  g.X += spec * nl;
+  g.st += nl;
   if (ny == nx) {
     switch (ny) {
 #define CASE(n) \

@@ -117,7 +117,10 @@ enum ccpt_dtype { CCPT_U16 = 0, CCPT_F32 = 1, CCPT_F64 = 2 };
                                replay it on later calls */
 #define CCPT_FLAG_PROFILE 2 /* bracket every kernel launch with HIP events on the
                                call's stream (measurement; disables graphs and
-                               CCPT_FLAG_STREAMS) */
+                               CCPT_FLAG_STREAMS, and runs the correlation of
+                               frames other than 256 x 256 as the three passes
+                               of stages 1-3, with the same results, where an
+                               untimed call may take them in one kernel) */
 #define CCPT_FLAG_STREAMS 4 /* run the chunks of a batch alternately on the call's
                                stream and a second stream owned by the context
                                (default priority), forked from and joined back

@@ -70,6 +70,12 @@ class Roi(ctypes.Structure):
                 ("ref_id", c_int)]
 
 
+#: Roi as a numpy record (the C layout)
+ROI_DTYPE = np.dtype([("data", "<u8"), ("ny", "<i4"), ("nx", "<i4"), ("pitch", "<i4"), ("dtype", "<i4"),
+                      ("ref_id", "<i4"), ("_pad", "<i4")])
+assert ROI_DTYPE.itemsize == ctypes.sizeof(Roi)
+
+
 class CcptError(RuntimeError):
     def __init__(self, code, msg):
         super().__init__(f"ccpt error {code}: {msg}")
@@ -226,13 +232,22 @@ class Tracker:
             if frames.stride(2) != 1:
                 raise ValueError("frame rows must be contiguous")
             n, ny, nx = frames.shape
-            ids = [0] * n if ref_ids is None else ref_ids
+            ids = (0,) * n if ref_ids is None else ref_ids
             base, step, es = frames.data_ptr(), frames.stride(0), frames.element_size()
             pitch, code = frames.stride(1), _dtype_code(frames)
-            arr = (Roi * n)()
-            for i in range(n):
-                arr[i] = Roi(base + i * step * es, ny, nx, pitch, code, int(ids[i]))
-            return arr, n
+            if n < 16:
+                arr = (Roi * n)()
+                for i in range(n):
+                    arr[i] = Roi(base + i * step * es, ny, nx, pitch, code, int(ids[i]))
+                return arr, n
+            # the same records filled column by column (a recording has
+            # thousands); the ctypes array shares the buffer's memory
+            rec = np.zeros(n, dtype=ROI_DTYPE)
+            rec["data"] = base + np.arange(n, dtype=np.int64) * (step * es)
+            rec["ny"], rec["nx"], rec["pitch"], rec["dtype"] = ny, nx, pitch, code
+            if ref_ids is not None:
+                rec["ref_id"] = [int(ids[i]) for i in range(n)]
+            return (Roi * n).from_buffer(rec), n
         else:
             seq = list(frames)
         n = len(seq)
@@ -280,7 +295,8 @@ class Tracker:
         gp = g_peak.to(self.device, torch.float64).contiguous() if g_peak is not None else None
         gf = gr = None
         if want_frames:
-            total = sum(arr[i].ny * arr[i].nx for i in range(n))
+            total = (n * frames.shape[-2] * frames.shape[-1] if isinstance(frames, torch.Tensor)
+                     else sum(arr[i].ny * arr[i].nx for i in range(n)))
             gf = torch.empty(total, dtype=torch.float32, device=self.device)
         if want_ref:
             total = sum(r.shape[0] * r.shape[1] for r in self._refs)

@@ -149,6 +149,11 @@ struct ccpt_ctx {
   hipStream_t lane_s[kMaxLanes - 1] = {};
   hipEvent_t lane_evt[kMaxLanes - 1] = {};
   int lanes = 0;  // most lanes a call uses (0: kMaxLanes)
+  // references: check flags, scratch spectrum
+  void* ref_flags = nullptr;
+  size_t ref_flags_cap = 0;
+  void* ref_tmp = nullptr;
+  size_t ref_tmp_cap = 0;
   // real-time updates: scratch spectra T and F
   void* rt_buf = nullptr;
   size_t rt_cap = 0;
@@ -208,6 +213,13 @@ int upload(ccpt_ctx* ctx, T*& dst, const std::vector<T>& src) {
   HIP_CHECK(ctx, hipMalloc(&dst, src.size() * sizeof(T)));
   HIP_CHECK(ctx, hipMemcpy(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
   return CCPT_OK;
+}
+
+// Frees a reference's buffers and leaves it without a shape.
+void free_ref(Ref& r) {
+  for (void* p : {(void*)r.spec, (void*)r.spec64, (void*)r.img, (void*)r.espec})
+    if (p) (void)hipFree(p);
+  r = Ref{};
 }
 
 void free_tables(SizeTables& t) {
@@ -766,12 +778,9 @@ void ccpt_destroy(ccpt_ctx* ctx) {
   for (auto& kv : ctx->tables) free_tables(kv.second);
   if (ctx->tf) (void)hipFree(ctx->tf);
   if (ctx->td) (void)hipFree(ctx->td);
-  for (auto& r : ctx->refs) {
-    (void)hipFree(r.spec);
-    if (r.spec64) (void)hipFree(r.spec64);
-    if (r.espec) (void)hipFree(r.espec);
-    (void)hipFree(r.img);
-  }
+  for (auto& r : ctx->refs) free_ref(r);
+  if (ctx->ref_flags) (void)hipFree(ctx->ref_flags);
+  if (ctx->ref_tmp) (void)hipFree(ctx->ref_tmp);
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->d_desc) (void)hipFree(ctx->d_desc);
   if (ctx->h_desc) (void)hipHostFree(ctx->h_desc);
@@ -809,14 +818,29 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
       return fail(ctx, CCPT_E_UNSUPPORTED, "reference %d: the fp16 split takes 256x256 frames only",
                   i);
   }
+  // everything queued is done with the old set, and whatever made the images,
+  // on any stream, has run
+  HIP_CHECK(ctx, hipDeviceSynchronize());
+  // the domain checks, on the device: one flag per reference
+  rc = ensure_buf(ctx, ctx->ref_flags, ctx->ref_flags_cap, (size_t)n_refs * sizeof(unsigned));
+  if (rc) return rc;
+  unsigned* flags = (unsigned*)ctx->ref_flags;
+  if (launch_zero(flags, (size_t)n_refs * sizeof(unsigned), s))
+    return fail(ctx, CCPT_E_HIP, "zero launch failed");
+  for (int i = 0; i < n_refs; ++i)
+    if (launch_ref_check(refs[i].data, refs[i].dtype, refs[i].pitch, refs[i].ny, refs[i].nx, ctx->o.mode,
+                         ctx->o.eps, flags + i, s))
+      return fail(ctx, CCPT_E_HIP, "reference check launch failed");
+  std::vector<unsigned> bad(n_refs);
+  HIP_CHECK(ctx, hipMemcpyAsync(bad.data(), flags, (size_t)n_refs * sizeof(unsigned),
+                                hipMemcpyDeviceToHost, s));
   HIP_CHECK(ctx, hipStreamSynchronize(s));
-  // read the references back: the CC-SN domain check and the context's own copy
-  std::vector<std::vector<double>> host(n_refs);
   for (int i = 0; i < n_refs; ++i) {
+    if (!bad[i]) continue;
+    // the first offending pixel, for the message
     const ccpt_image& im = refs[i];
     std::vector<char> raw(((size_t)(im.ny - 1) * im.pitch + im.nx) * dtype_bytes(im.dtype));
     HIP_CHECK(ctx, hipMemcpy(raw.data(), im.data, raw.size(), hipMemcpyDeviceToHost));
-    host[i].resize((size_t)im.ny * im.nx);
     for (int y = 0; y < im.ny; ++y)
       for (int x = 0; x < im.nx; ++x) {
         const double v = pixel(raw.data(), im.dtype, (size_t)y * im.pitch + x);
@@ -825,87 +849,65 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
         if (ctx->o.mode == CCPT_MODE_CCSN && !(v + ctx->o.eps > 0.0))
           return fail(ctx, CCPT_E_NONPOSITIVE_REF, "reference %d: E + eps <= 0 at (%d, %d)", i,
                       y, x);
-        host[i][(size_t)y * im.nx + x] = v;
       }
+    return fail(ctx, CCPT_E_INVALID, "reference %d changed while it was read", i);
   }
-  // drop the old set (graphs hold pointers to the old spectra through descriptors only)
-  HIP_CHECK(ctx, hipDeviceSynchronize());
-  for (auto& r : ctx->refs) {
-    (void)hipFree(r.spec);
-    if (r.spec64) (void)hipFree(r.spec64);
-    if (r.espec) (void)hipFree(r.espec);
-    (void)hipFree(r.img);
-  }
-  ctx->refs.clear();
   ctx->last_desc.clear();
-  // scratch: one spectrum (FP64 size) plus the FP64 image of the FP64 mode
+  // scratch: one spectrum (FP64 size)
   size_t tmp_need = 0;
   for (int i = 0; i < n_refs; ++i) {
     const int code = shape_code(refs[i].ny, refs[i].nx);
-    tmp_need = std::max(tmp_need, spec_elems(code) * sizeof(double2) +
-                                      (size_t)refs[i].ny * refs[i].nx * sizeof(double));
+    tmp_need = std::max(tmp_need, spec_elems(code) * sizeof(double2));
     rc = ensure_tables(ctx, code);
     if (rc) return rc;
   }
-  char* tmp = nullptr;
-  HIP_CHECK(ctx, hipMalloc(&tmp, tmp_need));
-  float2* T = (float2*)tmp;
+  rc = ensure_buf(ctx, ctx->ref_tmp, ctx->ref_tmp_cap, tmp_need);
+  if (rc) return rc;
+  float2* T = (float2*)ctx->ref_tmp;
+  double2* T64 = (double2*)ctx->ref_tmp;
+  // a reference of the same shape takes over its predecessor's buffers; from
+  // the first failure on there are no references
+  auto drop_from = [&](size_t k) {
+    for (size_t r = k; r < ctx->refs.size(); ++r) free_ref(ctx->refs[r]);
+    ctx->refs.resize(std::min(k, ctx->refs.size()));
+  };
+  drop_from(n_refs);
+  const int weight = ctx->o.mode == CCPT_MODE_CCSN ? 1 : 0;
   for (int i = 0; i < n_refs; ++i) {
-    const int n = refs[i].nx;  // (square frames: the size)
-    const int code = shape_code(refs[i].ny, refs[i].nx);
-    const size_t npx = (size_t)refs[i].ny * refs[i].nx;
+    const ccpt_image& im = refs[i];
+    const int code = shape_code(im.ny, im.nx);
+    const size_t npx = (size_t)im.ny * im.nx, spec = spec_elems(code);
     const SizeTables& st = ctx->tables[table_key(code)];
-    Ref r;
-    r.n = code;
-    if (hipMalloc(&r.spec, spec_elems(code) * sizeof(float2)) != hipSuccess ||
-        hipMalloc(&r.img, npx * sizeof(float)) != hipSuccess ||
-        (fp64(ctx) && hipMalloc(&r.spec64, spec_elems(n) * sizeof(double2)) != hipSuccess)) {
-      (void)hipFree(tmp);
-      if (r.spec) (void)hipFree(r.spec);
-      if (r.img) (void)hipFree(r.img);
-      return fail(ctx, CCPT_E_NOMEM, "reference spectra");
-    }
-    ctx->refs.push_back(r);
-    std::vector<float> img32(host[i].begin(), host[i].end());
-    HIP_CHECK(ctx, hipMemcpy(r.img, img32.data(), npx * sizeof(float), hipMemcpyHostToDevice));
-    const int weight = ctx->o.mode == CCPT_MODE_CCSN ? 1 : 0;
-    // the image is stored as given (pitch nx); a wide one is read transposed
-    if (launch_spectrum(code_ny(code), code_nx(code), r.img, CCPT_F32, refs[i].nx, 0,
-                        code_trans(code), 1, weight, (float)ctx->o.eps, 1, T, r.spec, st.tw, s)) {
-      (void)hipFree(tmp);
-      return fail(ctx, CCPT_E_HIP, "reference spectrum launch failed");
-    }
-    if (ctx->o.mode == CCPT_MODE_CCSN) {
-      // F[E] itself (held tall), the state of real-time updates (B = -1/(E+eps)
-      // is not linear in E)
-      Ref& rr = ctx->refs.back();
-      if (hipMalloc(&rr.espec, spec_elems(code) * sizeof(float2)) != hipSuccess) {
-        (void)hipFree(tmp);
+    if ((size_t)i == ctx->refs.size()) ctx->refs.emplace_back();
+    Ref& r = ctx->refs[i];
+    if (r.n != code) {
+      free_ref(r);
+      r.n = code;
+      if (hipMalloc(&r.spec, spec * sizeof(float2)) != hipSuccess ||
+          hipMalloc(&r.img, npx * sizeof(float)) != hipSuccess ||
+          (fp64(ctx) && hipMalloc(&r.spec64, spec * sizeof(double2)) != hipSuccess) ||
+          (weight && hipMalloc(&r.espec, spec * sizeof(float2)) != hipSuccess)) {
+        drop_from(i);
         return fail(ctx, CCPT_E_NOMEM, "reference spectra");
       }
-      HIP_CHECK(ctx, hipStreamSynchronize(s));
-      if (launch_spectrum(code_ny(code), code_nx(code), r.img, CCPT_F32, refs[i].nx, 0,
-                          code_trans(code), 1, 0, 0.f, 0, T, rr.espec, st.tw, s)) {
-        (void)hipFree(tmp);
-        return fail(ctx, CCPT_E_HIP, "reference spectrum launch failed");
-      }
     }
-    if (fp64(ctx)) {
-      // the FP64 spectrum from the reference's own values, not their FP32 copy
-      double2* T64 = (double2*)tmp;
-      double* img64 = (double*)(T64 + spec_elems(n));
-      HIP_CHECK(ctx, hipStreamSynchronize(s));
-      HIP_CHECK(ctx, hipMemcpy(img64, host[i].data(), (size_t)n * n * sizeof(double),
-                               hipMemcpyHostToDevice));
-      if (launch_spectrum64(n, img64, CCPT_F64, n, 0, 1, weight, ctx->o.eps, 1, T64, r.spec64,
-                            ctx->tables[n].tw64, s)) {
-        (void)hipFree(tmp);
-        return fail(ctx, CCPT_E_HIP, "reference spectrum launch failed");
-      }
+    const int ny = code_ny(code), nx = code_nx(code), tr = code_trans(code);
+    // the context's float copy is stored as given (pitch nx), a wide one read
+    // transposed; CC-SN keeps F[E] too (held tall), the state of real-time
+    // updates (B = -1/(E+eps) is not linear in E); the FP64 spectrum comes
+    // from the reference's own values
+    if (launch_ref_copy(im.data, im.dtype, im.pitch, im.ny, im.nx, r.img, s) ||
+        launch_spectrum(ny, nx, r.img, CCPT_F32, im.nx, 0, tr, 1, weight, (float)ctx->o.eps, 1, T, r.spec,
+                        st.tw, s) ||
+        (weight && launch_spectrum(ny, nx, r.img, CCPT_F32, im.nx, 0, tr, 1, 0, 0.f, 0, T, r.espec, st.tw, s)) ||
+        (fp64(ctx) && launch_spectrum64(im.nx, im.data, im.dtype, im.pitch, 0, 1, weight, ctx->o.eps, 1, T64,
+                                        r.spec64, st.tw64, s))) {
+      (void)hipStreamSynchronize(s);
+      drop_from(i);
+      return fail(ctx, CCPT_E_HIP, "reference spectrum launch failed");
     }
-    HIP_CHECK(ctx, hipStreamSynchronize(s));
   }
-  HIP_CHECK(ctx, hipFree(tmp));
+  HIP_CHECK(ctx, hipStreamSynchronize(s));
   return CCPT_OK;
 }
 

@@ -313,6 +313,11 @@ int launch_align_accumulate(int N, const FrameDesc* desc, int first, int count,
 // swap in that layout).
 int launch_rt_update(int ny, int nx, int trans, const ccpt_result* res, const float2* F, float2* S,
                      float a0, float b1, int conj_s, hipStream_t s);
+// References: sets *flag (zeroed before) if a pixel is not finite or, in CC-SN,
+// E + eps <= 0; the float copy [ny][nx] of an image.
+int launch_ref_check(const void* data, int dtype, int pitch, int ny, int nx, int mode, double eps,
+                     unsigned* flag, hipStream_t s);
+int launch_ref_copy(const void* data, int dtype, int pitch, int ny, int nx, float* img, hipStream_t s);
 // img *= scale / *cnt (zeros when *cnt == 0).
 int launch_scale_by_count(float* img, int nn, float scale, const unsigned* cnt, hipStream_t s);
 

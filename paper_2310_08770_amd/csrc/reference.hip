@@ -182,4 +182,40 @@ int launch_scale_by_count(float* img, int nn, float scale, const unsigned* cnt, 
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
+// ------------------------------------------------------------ references
+__device__ __forceinline__ double ref_px(const void* p, int dtype, size_t idx) {
+  if (dtype == CCPT_U16) return (double)((const unsigned short*)p)[idx];
+  if (dtype == CCPT_F64) return ((const double*)p)[idx];
+  return (double)((const float*)p)[idx];
+}
+
+__global__ void k_ref_check(const void* __restrict__ data, int dtype, int pitch, int ny, int nx, int mode,
+                            double eps, unsigned* __restrict__ flag) {
+  bool bad = false;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ny * nx; i += gridDim.x * blockDim.x) {
+    const double v = ref_px(data, dtype, (size_t)(i / nx) * pitch + i % nx);
+    bad |= !isfinite(v) || (mode == CCPT_MODE_CCSN && !(v + eps > 0.0));
+  }
+  if (bad) *flag = 1u;  // (every writer stores the same value)
+}
+
+__global__ void k_ref_copy(const void* __restrict__ data, int dtype, int pitch, int ny, int nx,
+                           float* __restrict__ img) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < ny * nx; i += gridDim.x * blockDim.x)
+    img[i] = (float)ref_px(data, dtype, (size_t)(i / nx) * pitch + i % nx);
+}
+
+int launch_ref_check(const void* data, int dtype, int pitch, int ny, int nx, int mode, double eps,
+                     unsigned* flag, hipStream_t s) {
+  const int blocks = (ny * nx + 1023) / 1024;  // four pixels per thread
+  hipLaunchKernelGGL(k_ref_check, dim3(blocks), dim3(256), 0, s, data, dtype, pitch, ny, nx, mode, eps, flag);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_ref_copy(const void* data, int dtype, int pitch, int ny, int nx, float* img, hipStream_t s) {
+  const int blocks = (ny * nx + 1023) / 1024;
+  hipLaunchKernelGGL(k_ref_copy, dim3(blocks), dim3(256), 0, s, data, dtype, pitch, ny, nx, img);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
 }  // namespace ccpt

@@ -58,8 +58,16 @@ __device__ __forceinline__ C mul_i(C a) {
 // so the strided writes of the early Stockham stages spread over the LDS
 // banks.  lds_len(n) slots hold a sequence of n elements.
 constexpr int kLdsPadShift = 4;
-__host__ __device__ constexpr int lds_idx(int i) {
+__host__ __device__ constexpr unsigned lds_idx(unsigned i) {
   return kLdsPadShift ? i + (i >> kLdsPadShift) : i;
+}
+// Whether lds_idx(i0 + t STEP) = lds_idx(i0) + lds_idx(t STEP) for every t of a
+// stage: STEP a multiple of the pad period, or (the Stockham write order, i0 =
+// k + a BLOCK with k < STEP) a divisor of it with BLOCK dividing or divided by
+// it.  The places of a butterfly's values are then constants apart.
+constexpr bool lds_step(unsigned step, unsigned block) {
+  constexpr unsigned p = 1u << kLdsPadShift;
+  return step % p == 0 || (block && p % step == 0 && (block % p == 0 || p % block == 0));
 }
 __host__ __device__ constexpr int lds_len(int n) {
   return kLdsPadShift ? n + (n >> kLdsPadShift) : n;
@@ -147,49 +155,51 @@ __device__ __forceinline__ void dft(C* v) {
 
 // One Stockham stage of radix R on `nseq` sequences of length L (sequence
 // q at src/dst + q*stride).  NS = product of the radices already applied.
-// tw: exp(-2 pi i m / NTW), m < NTW, with L | NTW.
-template <int L, int R, int SIGN, int NTW, typename C>
+// tw: exp(-2 pi i m / NTW), m < NTW, with L | NTW.  (Unsigned throughout: the
+// divisions are by constants, and shifts for powers of two.)
+template <int L, int R, int SIGN, int NTW, int NS, typename C>
 __device__ __forceinline__ void fft_stage(const C* __restrict__ src, C* __restrict__ dst,
-                                          int nseq, int stride, int NS, const C* tw,
-                                          int tid, int nthr) {
-  constexpr int B = L / R;
-  const int total = nseq * B;
-  for (int b = tid; b < total; b += nthr) {
-    const int q = b / B;
-    const int j = b - q * B;
+                                          unsigned nseq, unsigned stride, const C* tw,
+                                          unsigned tid, unsigned nthr) {
+  constexpr unsigned B = L / R;
+  constexpr bool RD = lds_step(B, 0), WR = lds_step(NS, NS * R);
+  const unsigned total = nseq * B;
+  for (unsigned b = tid; b < total; b += nthr) {
+    const unsigned q = b / B, j = b % B;
     const C* in = src + q * stride;
     C* out = dst + q * stride;
     C v[R];
+    const unsigned j0 = lds_idx(j);
 #pragma unroll
-    for (int t = 0; t < R; ++t) v[t] = in[lds_idx(j + t * B)];
-    const int k = j % NS;
+    for (unsigned t = 0; t < R; ++t) v[t] = in[RD ? j0 + lds_idx(t * B) : lds_idx(j + t * B)];
+    const unsigned k = j % NS;
     if (NS > 1) {
       // twiddle exp(SIGN * 2 pi i t k / (NS R)) = tw[t k NTW / (NS R)] (conj for SIGN > 0)
-      const int step = NTW / (NS * R);
+      constexpr unsigned step = NTW / (NS * R);
 #pragma unroll
-      for (int t = 1; t < R; ++t) {
+      for (unsigned t = 1; t < R; ++t) {
         C w = tw[t * k * step];
         if (SIGN > 0) w.y = -w.y;
         v[t] = cmul(v[t], w);
       }
     }
     dft<R, SIGN>(v);
-    const int base = (j / NS) * NS * R + k;
+    const unsigned base = j / NS * (NS * R) + k, base0 = lds_idx(base);
 #pragma unroll
-    for (int t = 0; t < R; ++t) out[lds_idx(base + t * NS)] = v[t];
+    for (unsigned t = 0; t < R; ++t) out[WR ? base0 + lds_idx(t * NS) : lds_idx(base + t * NS)] = v[t];
   }
 }
 
-template <int L, int SIGN, int NTW, int ST, typename C>
-__device__ __forceinline__ C* fft_run(C* a, C* b, int nseq, int stride, int NS, const C* tw,
-                                      int tid, int nthr) {
+template <int L, int SIGN, int NTW, int ST, int NS, typename C>
+__device__ __forceinline__ C* fft_run(C* a, C* b, unsigned nseq, unsigned stride, const C* tw, unsigned tid,
+                                      unsigned nthr) {
   if constexpr (ST == fft_stages(L)) {
     return a;
   } else {
     constexpr int R = fft_radix(L, ST);
-    fft_stage<L, R, SIGN, NTW>(a, b, nseq, stride, NS, tw, tid, nthr);
+    fft_stage<L, R, SIGN, NTW, NS>(a, b, nseq, stride, tw, tid, nthr);
     __syncthreads();
-    return fft_run<L, SIGN, NTW, ST + 1>(b, a, nseq, stride, NS * R, tw, tid, nthr);
+    return fft_run<L, SIGN, NTW, ST + 1, NS * R>(b, a, nseq, stride, tw, tid, nthr);
   }
 }
 
@@ -197,7 +207,7 @@ __device__ __forceinline__ C* fft_run(C* a, C* b, int nseq, int stride, int NS, 
 // the buffer holding the result.  Callers must __syncthreads() before.
 template <int L, int SIGN, int NTW, typename C>
 __device__ __forceinline__ C* fft_lds(C* a, C* b, int nseq, int stride, const C* tw) {
-  return fft_run<L, SIGN, NTW, 0>(a, b, nseq, stride, 1, tw, threadIdx.x, blockDim.x);
+  return fft_run<L, SIGN, NTW, 0, 1>(a, b, nseq, stride, tw, threadIdx.x, blockDim.x);
 }
 
 }  // namespace ccpt

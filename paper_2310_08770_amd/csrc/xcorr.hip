@@ -91,16 +91,6 @@ __device__ __forceinline__ void img_of(const ImgSrc& s, int f, const void*& data
   }
 }
 
-template <typename T>
-__device__ __forceinline__ T wave_max_u64(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    T w = __shfl_xor(v, o, 64);
-    v = w > v ? w : v;
-  }
-  return v;
-}
-
 __device__ __forceinline__ unsigned wave_min_u32(unsigned v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = min(v, (unsigned)__shfl_xor((int)v, o, 64));
@@ -143,10 +133,10 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
   __shared__ C bufA[RPB * LS];
   __shared__ C bufB[RPB * LS];
   __shared__ unsigned red[3][kThreads / 64];
-  const int tid = threadIdx.x;
+  const unsigned tid = threadIdx.x;
   const int f = blockIdx.y;
   const int y0 = blockIdx.x * RPB;
-  for (int i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
+  for (unsigned i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
   const void* data;
   int dtype, pitch;
   img_of(src, f, data, dtype, pitch);
@@ -166,8 +156,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
                      ((uintptr_t)data & 15) == 0;
   if (vec16) {
     // 8 pixels (16 bytes) per load
-    for (int i = tid; i < RPB * (NX / 8); i += kThreads) {
-      const int r = i / (NX / 8), q = i - r * (NX / 8);
+    for (unsigned i = tid; i < (unsigned)(RPB * (NX / 8)); i += kThreads) {
+      const unsigned r = i / (NX / 8), q = i % (NX / 8);
       const uint4 v = *(const uint4*)((const unsigned short*)data + (long)(y0 + r) * pitch + 8 * q);
       const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -175,8 +165,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
         bufA[r * LS + lds_idx(4 * q + e)] = mkc<C>(pro((R)(w[e] & 0xFFFFu)), pro((R)(w[e] >> 16)));
     }
   } else if (vec32) {
-    for (int i = tid; i < RPB * (NX / 4); i += kThreads) {
-      const int r = i / (NX / 4), q = i - r * (NX / 4);
+    for (unsigned i = tid; i < (unsigned)(RPB * (NX / 4)); i += kThreads) {
+      const unsigned r = i / (NX / 4), q = i % (NX / 4);
       const float4 v = *(const float4*)((const float*)data + (long)(y0 + r) * pitch + 4 * q);
       bufA[r * LS + lds_idx(2 * q)] = mkc<C>(pro((R)v.x), pro((R)v.y));
       bufA[r * LS + lds_idx(2 * q + 1)] = mkc<C>(pro((R)v.z), pro((R)v.w));
@@ -184,16 +174,16 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
   } else if (trans) {
     // row y of the tall image is column y of the wide frame: adjacent threads
     // take adjacent columns of one frame row
-    for (int i = tid; i < RPB * L; i += kThreads) {
-      const int c = i / RPB, r = i - c * RPB;
+    for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+      const unsigned c = i / RPB, r = i % RPB;
       const long idx = (long)(2 * c) * pitch + (y0 + r);
       const R a0 = pro(load_px<R>(data, dtype, idx));
       const R a1 = pro(load_px<R>(data, dtype, idx + pitch));
       bufA[r * LS + lds_idx(c)] = mkc<C>(a0, a1);
     }
   } else {
-    for (int i = tid; i < RPB * L; i += kThreads) {
-      const int r = i / L, c = i - r * L;
+    for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+      const unsigned r = i / L, c = i % L;
       const long idx = (long)(y0 + r) * pitch + 2 * c;
       const R a0 = pro(load_px<R>(data, dtype, idx));
       const R a1 = pro(load_px<R>(data, dtype, idx + 1));
@@ -227,8 +217,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
   // T[k][y] so each column k receives RPB consecutive rows
   C* Tf = T + (size_t)f * NY * H;
   const R half = R(0.5);
-  for (int i = tid; i < RPB * H; i += kThreads) {
-    const int k = i / RPB, r = i - k * RPB;
+  for (unsigned i = tid; i < (unsigned)(RPB * H); i += kThreads) {
+    const unsigned k = i / RPB, r = i % RPB;
     const C zk = z[r * LS + lds_idx(k == L ? 0 : k)];
     const C zc = cconj(z[r * LS + lds_idx(k == 0 ? 0 : L - k)]);
     const C e = cscale(cadd(zk, zc), half);
@@ -258,7 +248,7 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
   __shared__ C tw[NY];
   __shared__ C bufA[CS * S];
   __shared__ C bufB[CS * S];
-  const int tid = threadIdx.x;
+  const unsigned tid = threadIdx.x;
   const int f = blockIdx.y;
   const int c0 = blockIdx.x * CB;
   const int nreg = min(CB, NC - c0);       // regular columns of this block
@@ -266,28 +256,70 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
   const int nseq = has_nyq ? CS : CB;
   // slot -> column index (-1 when empty)
   auto col_of = [&](int c) { return c < nreg ? c0 + c : (c == CB && has_nyq ? NC : -1); };
-  for (int i = tid; i < NY; i += kThreads) tw[i] = gtw[i];
+  for (unsigned i = tid; i < NY; i += kThreads) tw[i] = gtw[i];
   // T is column-major: column kx holds NY consecutive rows
   C* Tf = T + (size_t)f * NY * H;
+  // every value a thread moves is requested before the first is used (one trip
+  // to memory, not one per value), the reference's with the spectrum's
+  constexpr int IT = (NY * CS + kThreads - 1) / kThreads;
+  const unsigned count = (unsigned)(NY * nseq);
+  // element i of this block: row-major (row y, slot c) for spectra, and
+  // column-major for T
+  auto row_of = [&](unsigned i, unsigned& y, unsigned& c) {
+    y = has_nyq ? i / CS : i / CB;
+    c = has_nyq ? i % CS : i % CB;
+  };
+  C in[IT], rv[KIND == COL_XCORR ? IT : 1];
   if constexpr (KIND == COL_INV) {
     const C* inp = spec + (size_t)f * spec_stride;  // row-major spectrum
-    for (int i = tid; i < NY * nseq; i += kThreads) {
-      const int y = i / nseq, c = i - y * nseq;
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      unsigned y, c;
+      row_of(min(tid + it * kThreads, count - 1), y, c);
       const int kx = col_of(c);
-      bufA[c * S + lds_idx(y)] = kx >= 0 ? inp[(size_t)y * H + kx] : mkc<C>(0, 0);
+      in[it] = inp[(size_t)y * H + (kx >= 0 ? kx : 0)];
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      unsigned y, c;
+      row_of(i, y, c);
+      if (i < count) {
+        const bool ok = col_of(c) >= 0;
+        bufA[c * S + lds_idx(y)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
+      }
     }
   } else {
-    for (int i = tid; i < NY * nseq; i += kThreads) {
-      const int c = i / NY, y = i - c * NY;
-      const int kx = col_of(c);
-      bufA[c * S + lds_idx(y)] = kx >= 0 ? Tf[(size_t)kx * NY + y] : mkc<C>(0, 0);
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = min(tid + it * kThreads, count - 1);
+      const int kx = col_of(i / NY);
+      in[it] = Tf[(size_t)(kx >= 0 ? kx : 0) * NY + i % NY];
+    }
+    if constexpr (KIND == COL_XCORR) {
+      const C* R = (const C*)desc[first + f].rspec;
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        unsigned y, c;
+        row_of(min(tid + it * kThreads, count - 1), y, c);
+        const int kx = col_of(c);
+        rv[it] = R[(size_t)y * H + (kx >= 0 ? kx : 0)];
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      if (i < count) {
+        const bool ok = col_of(i / NY) >= 0;
+        bufA[i / NY * S + lds_idx(i % NY)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
+      }
     }
   }
   __syncthreads();
   if constexpr (KIND == COL_INV) {
     C* r = fft_lds<NY, +1, NY>(bufA, bufB, nseq, S, tw);
-    for (int i = tid; i < NY * nseq; i += kThreads) {
-      const int c = i / NY, y = i - c * NY;
+    for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
+      const unsigned c = i / NY, y = i % NY;
       const int kx = col_of(c);
       if (kx >= 0) Tf[(size_t)kx * NY + y] = r[c * S + lds_idx(y)];
     }
@@ -295,8 +327,8 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
     C* r = fft_lds<NY, -1, NY>(bufA, bufB, nseq, S, tw);
     if constexpr (KIND == COL_FWD || KIND == COL_FWD_CONJ) {
       C* out = spec + (size_t)f * spec_stride;
-      for (int i = tid; i < NY * nseq; i += kThreads) {
-        const int y = i / nseq, c = i - y * nseq;
+      for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
+        const unsigned y = has_nyq ? i / CS : i / CB, c = has_nyq ? i % CS : i % CB;
         const int kx = col_of(c);
         if (kx >= 0) {
           C v = r[c * S + lds_idx(y)];
@@ -305,24 +337,27 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
         }
       }
     } else {
-      const C* R = (const C*)desc[first + f].rspec;
       C* Xf = X + (size_t)f * NY * H;
-      for (int i = tid; i < NY * nseq; i += kThreads) {
-        const int y = i / nseq, c = i - y * nseq;
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const unsigned i = tid + it * kThreads;
+        unsigned y, c;
+        row_of(i, y, c);
         const int kx = col_of(c);
-        if (kx >= 0) {
-          const C v = cmul(r[c * S + lds_idx(y)], R[(size_t)y * H + kx]);
-          Xf[(size_t)y * H + kx] = v;
+        if (i < count) {
+          C v = zero;
+          if (kx >= 0) {
+            v = cmul(r[c * S + lds_idx(y)], rv[it]);
+            Xf[(size_t)y * H + kx] = v;
+          }
           r[c * S + lds_idx(y)] = v;
-        } else {
-          r[c * S + lds_idx(y)] = zero;
         }
       }
       __syncthreads();
       C* o = (r == bufA) ? bufB : bufA;
       C* q = fft_lds<NY, +1, NY>(r, o, nseq, S, tw);
-      for (int i = tid; i < NY * nseq; i += kThreads) {
-        const int c = i / NY, y = i - c * NY;
+      for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
+        const unsigned c = i / NY, y = i % NY;
         const int kx = col_of(c);
         if (kx >= 0) Tf[(size_t)kx * NY + y] = q[c * S + lds_idx(y)];
       }
@@ -349,20 +384,33 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   constexpr int L = NX / 2, H = NX / 2 + 1;
   constexpr int LS = lds_len(L) + 1;
   __shared__ C tw[NX];
-  __shared__ C raw[RPB * H];
   __shared__ C bufA[RPB * LS];
   __shared__ C bufB[RPB * LS];
-  __shared__ unsigned long long red[kThreads / 64], red2[kThreads / 64];
+  static_assert(LS >= H, "bins fit bufB");
+  C* const raw = bufB;  // the bins as read, until they are packed into bufA
+  __shared__ float redf[2][kThreads / 64];
+  __shared__ unsigned redu[kThreads / 64];
   __shared__ double redv[kThreads / 64], redv2[kThreads / 64];
-  const int tid = threadIdx.x;
+  const unsigned tid = threadIdx.x;
   const int f = blockIdx.y;
   const int y0 = blockIdx.x * RPB;
-  for (int i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
-  // column-major T: column k holds rows y0..y0+RPB-1 consecutively
+  for (unsigned i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
+  // column-major T: column k holds rows y0..y0+RPB-1 consecutively; all loads
+  // before the first use
   const C* Tf = T + (size_t)f * NY * H + y0;
-  for (int i = tid; i < RPB * H; i += kThreads) {
-    const int k = i / RPB, r = i - k * RPB;
-    raw[r * H + k] = Tf[(size_t)k * NY + r];
+  {
+    constexpr int IT = (RPB * H + kThreads - 1) / kThreads;
+    C in[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * H - 1));
+      in[it] = Tf[(size_t)(i / RPB) * NY + i % RPB];
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      if ((RPB * H) % kThreads == 0 || i < (unsigned)(RPB * H)) raw[i % RPB * H + i / RPB] = in[it];
+    }
   }
   // frame row-major index of tall pixel (y, x), and the step to (y, x + 1)
   const bool trans = transposed<NY, NX>(trans_in);
@@ -372,8 +420,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   const unsigned xstep = trans ? (unsigned)NY : 1u;
   __syncthreads();
   const R half = R(0.5);
-  for (int i = tid; i < RPB * L; i += kThreads) {
-    const int r = i / L, k = i - r * L;
+  for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+    const unsigned r = i / L, k = i % L;
     const C xk = raw[r * H + k];
     const C xc = cconj(raw[r * H + L - k]);
     const C e = cscale(cadd(xk, xc), half);
@@ -383,40 +431,60 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   __syncthreads();
   C* z = fft_lds<L, +1, NX>(bufA, bufB, RPB, LS, tw);
   if constexpr (ARGMAX && !FP64) {
-    // the two largest keys of the block (keys are unique: they hold the index)
-    unsigned long long best = 0, second = 0;
-    auto push = [&](unsigned long long k) {  // branch-free top-two insertion
-      const unsigned long long lo = k < best ? k : best;
-      best = k < best ? best : k;
-      second = second < lo ? lo : second;
-    };
-    for (int i = tid; i < RPB * L; i += kThreads) {
-      const int r = i / L, n = i - r * L;
-      const C v = z[r * LS + lds_idx(n)];
-      const unsigned flat = flat_of(y0 + r, 2 * n);
-      push(peak_key(v.x, flat));
-      push(peak_key(v.y, flat + xstep));
-    }
+    // the two largest values of the block (equal ones count twice), then the
+    // lowest frame row-major index that holds the largest
+    constexpr int IT = (RPB * L + kThreads - 1) / kThreads;
+    C w[IT];
+    float t1 = -__builtin_inff(), t2 = t1;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const unsigned long long b1 = __shfl_xor(best, o, 64), b2 = __shfl_xor(second, o, 64);
-      const unsigned long long lo = b1 < best ? b1 : best;
-      second = second > b2 ? second : b2;
-      second = second > lo ? second : lo;
-      best = b1 > best ? b1 : best;
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      w[it] = mkc<C>(-__builtin_inff(), -__builtin_inff());
+      if ((RPB * L) % kThreads == 0 || i < (unsigned)(RPB * L)) w[it] = z[i / L * LS + lds_idx(i % L)];
+      float lo = fminf(t1, w[it].x);
+      t1 = fmaxf(t1, w[it].x);
+      t2 = fmaxf(t2, lo);
+      lo = fminf(t1, w[it].y);
+      t1 = fmaxf(t1, w[it].y);
+      t2 = fmaxf(t2, lo);
     }
+    const float mine = t1;
+    auto merge2 = [&](float b1, float b2) {
+      const float lo = fminf(t1, b1);
+      t1 = fmaxf(t1, b1);
+      t2 = fmaxf(fmaxf(t2, b2), lo);
+    };
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) merge2(__shfl_xor(t1, o, 64), __shfl_xor(t2, o, 64));
     if ((tid & 63) == 0) {
-      red[tid >> 6] = best;
-      red2[tid >> 6] = second;
+      redf[0][tid >> 6] = t1;
+      redf[1][tid >> 6] = t2;
     }
     __syncthreads();
-    if (tid == 0) {
-      for (int w = 1; w < kThreads / 64; ++w) {
-        push(red[w]);
-        push(red2[w]);
+    t1 = redf[0][0];
+    t2 = redf[1][0];
+#pragma unroll
+    for (int q = 1; q < kThreads / 64; ++q) merge2(redf[0][q], redf[1][q]);
+    unsigned idx = 0xFFFFFFFFu;
+    if (mine == t1) {  // (few threads hold the maximum)
+#pragma unroll
+      for (int it = 0; it < IT; ++it) {
+        const unsigned i = tid + it * kThreads;
+        if ((RPB * L) % kThreads == 0 || i < (unsigned)(RPB * L)) {
+          const unsigned flat = flat_of(y0 + i / L, 2 * (i % L));
+          if (__float_as_uint(w[it].x) == __float_as_uint(t1)) idx = min(idx, flat);
+          if (__float_as_uint(w[it].y) == __float_as_uint(t1)) idx = min(idx, flat + xstep);
+        }
       }
+    }
+    idx = wave_min_u32(idx);
+    if ((tid & 63) == 0) redu[tid >> 6] = idx;
+    __syncthreads();
+    if (tid == 0) {
+      for (int q = 1; q < kThreads / 64; ++q) idx = min(idx, redu[q]);
       // the frame's runner-up is some block's second or the smaller of two
       // block maxima meeting in the atomic: submit both
+      const unsigned long long best = peak_key(t1, idx), second = peak_key(t2, 0u);
       const unsigned long long old = atomicMax(&st[f].peak_key, best);
       const unsigned long long lose = old < best ? old : best;
       atomicMax(&st[f].second_key, second > lose ? second : lose);
@@ -435,8 +503,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
         sv = v;
       }
     };
-    for (int i = tid; i < RPB * L; i += kThreads) {
-      const int r = i / L, n = i - r * L;
+    for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+      const unsigned r = i / L, n = i % L;
       const C v = z[r * LS + lds_idx(n)];
       const unsigned flat = flat_of(y0 + r, 2 * n);
       take(v.x, flat);
@@ -452,12 +520,12 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
     if ((tid & 63) == 0) {
       redv[tid >> 6] = bv;
       redv2[tid >> 6] = sv;
-      red[tid >> 6] = bi;
+      redu[tid >> 6] = bi;
     }
     __syncthreads();
     if (tid == 0) {
       for (int w = 1; w < kThreads / 64; ++w) {
-        take(redv[w], (unsigned)red[w]);
+        take(redv[w], redu[w]);
         sv = redv2[w] > sv ? redv2[w] : sv;
       }
       PeakCand pc;
@@ -469,8 +537,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
     }
   } else if constexpr (!FP64) {
     float* out = img + (size_t)f * NY * NX + (size_t)y0 * NX;
-    for (int i = tid; i < RPB * L; i += kThreads) {
-      const int r = i / L, n = i - r * L;
+    for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+      const unsigned r = i / L, n = i % L;
       const C v = z[r * LS + lds_idx(n)];
       out[r * NX + 2 * n] = v.x * scale;
       out[r * NX + 2 * n + 1] = v.y * scale;

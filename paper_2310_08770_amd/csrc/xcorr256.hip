@@ -120,6 +120,7 @@ __device__ __forceinline__ float2 conjf2(float2 a) { return make_float2(a.x, -a.
 // the LDS waits would also have to wait for.
 typedef const unsigned long long __attribute__((address_space(1)))* gcf2;  // float2 pairs
 typedef const float __attribute__((address_space(1)))* gcf;
+typedef const char __attribute__((address_space(1)))* gcc;
 typedef const unsigned short __attribute__((address_space(1)))* gcu16;
 
 __device__ __forceinline__ float2 ld2(gcf2 p) {
@@ -142,6 +143,22 @@ __device__ __forceinline__ float2 c2r_bin(float2 a, float2 b, float2 w) {
   const float dx = 0.5f * (a.x - b.x), dy = 0.5f * (a.y + b.y);
   const float ox = dx * w.x - dy * w.y, oy = dx * w.y + dy * w.x;
   return make_float2(ex - oy, ey + ox);
+}
+
+// The thread index anew for each phase: offsets formed from it in one phase
+// and kept for another would fill the registers.
+__device__ __forceinline__ int fresh(int t) {
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
+// Orders a wave's LDS writes before its own later reads (of other lanes'
+// values) and the reads before later writes.  A wave's LDS instructions run in
+// order, so only the compiler has to be held; used where the values a wave
+// exchanges are its own rows' and no other wave touches them.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 template <typename T>
@@ -173,14 +190,17 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   // thread (n2 = t % 8, rq = t / 8): rows rq + 64 j, pairs 8 n1 + n2
   unsigned kmin = 0xFFFFFFFFu, kmax = 0u, bad;
   {
-    const int n2 = t & 7, rq = t >> 3;
+    const int tt = fresh(t), n2 = tt & 7, rq = tt >> 3;
     const float eps = g.eps;
-    auto take = [&](float2 a, int e) {
+    // POS: A >= 0 (uint16 frames, and squares), whose float bits order as
+    // unsigned integers; else order-preserving keys
+    auto take = [&](float2 a, int e, auto pos) {
+      constexpr bool POS = SN || decltype(pos)::value;
       if (SN) {
         a.x = (a.x + eps) * (a.x + eps);
         a.y = (a.y + eps) * (a.y + eps);
       }
-      const unsigned k0 = f2key(a.x), k1 = f2key(a.y);
+      const unsigned k0 = POS ? __float_as_uint(a.x) : f2key(a.x), k1 = POS ? __float_as_uint(a.y) : f2key(a.y);
       kmin = min(kmin, min(k0, k1));
       kmax = max(kmax, max(k0, k1));
       r[e] = a;
@@ -197,7 +217,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         for (int n1 = 0; n1 < 16; ++n1)
           raw[j * 16 + n1] = *(const unsigned __attribute__((address_space(1)))*)(b + 64 * j * p + 16 * n1);
 #pragma unroll
-      for (int e = 0; e < 64; ++e) take(make_float2((float)(raw[e] & 0xFFFFu), (float)(raw[e] >> 16)), e);
+      for (int e = 0; e < 64; ++e) take(make_float2((float)(raw[e] & 0xFFFFu), (float)(raw[e] >> 16)), e, std::true_type());
     } else {
       const gcf b = (gcf)desc.data + (size_t)rq * p + 2 * n2;
 #pragma unroll
@@ -205,13 +225,18 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
 #pragma unroll
         for (int n1 = 0; n1 < 16; ++n1) r[j * 16 + n1] = ld2((gcf2)(b + 64 * j * p + 16 * n1));
 #pragma unroll
-      for (int e = 0; e < 64; ++e) take(r[e], e);
+      for (int e = 0; e < 64; ++e) take(r[e], e, std::false_type());
+    }
+    if (SN || desc.dtype == CCPT_U16) {
+      // to keys (a NaN's is above +inf's, whatever its sign was)
+      kmin |= 0x80000000u;
+      kmax |= 0x80000000u;
     }
   }
   __syncthreads();  // twiddle table
   // ---------------------------------------------------------------- R1
   {
-    const int n2 = t & 7;
+    const int tt = fresh(t), n2 = tt & 7;
     float2 w[16];
 #pragma unroll
     for (int k1 = 1; k1 < 16; ++k1) w[k1] = tw[(2 * n2 * k1) & 255];
@@ -223,10 +248,11 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
     }
   }
   // ---------------------------------------------------------------- E2: rows
+  // (thread t takes rows t / 8 + 64 j on both sides: a wave's rows are its own)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     {
-      const int n2 = t & 7, rq = t >> 3;
+      const int tt = fresh(t), n2 = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int j = 2 * h + jj, yl = rq + 64 * jj;
@@ -234,9 +260,9 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         for (int k1 = 0; k1 < 16; ++k1) lds[yl * RS2 + e2pos(k1, n2)] = r[j * 16 + k1];
       }
     }
-    __syncthreads();
+    wave_order();
     {
-      const int gg = t & 7, rq = t >> 3;
+      const int tt = fresh(t), gg = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int j = 2 * h + jj, yl = rq + 64 * jj;
@@ -253,11 +279,11 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         }
       }
     }
-    __syncthreads();
+    wave_order();
   }
   // ---------------------------------------------------------------- R2 + unpack
   {
-    const int gg = t & 7;
+    const int tt = fresh(t), gg = tt & 7;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -297,8 +323,9 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   // ---------------------------------------------------------------- E3: rows -> columns
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
+    __syncthreads();  // the previous exchange's reads are done
     {
-      const int gg = t & 7, rq = t >> 3;
+      const int tt = fresh(t), gg = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -311,7 +338,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
     }
     __syncthreads();
     {
-      const int b = t & 15, cq = t >> 4;
+      const int tt = fresh(t), b = tt & 15, cq = tt >> 4;
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii) {
         const int cl = cq + 32 * ii;
@@ -319,11 +346,10 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         for (int a = 0; a < 16; ++a) r[pslot(ii * 16 + a, h)] = lds[cl * CS + 16 * a + b];
       }
     }
-    __syncthreads();
   }
   // ---------------------------------------------------------------- C1
   {
-    const int b = t & 15;
+    const int tt = fresh(t), b = tt & 15;
     float2 w[16];
 #pragma unroll
     for (int c = 1; c < 16; ++c) w[c] = tw[(b * c) & 255];
@@ -343,8 +369,9 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   // C2 thread: hp = t / 64 (c pair, uniform per wave), cp = t % 64 (columns cp, cp + 64)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
+    __syncthreads();  // the previous exchange's reads are done
     {
-      const int b = t & 15, cq = t >> 4;
+      const int tt = fresh(t), b = tt & 15, cq = tt >> 4;
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii) {
         const int cl = cq + 32 * ii;
@@ -354,7 +381,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
     }
     __syncthreads();
     {
-      const int hp = t >> 6, cp = t & 63;
+      const int tt = fresh(t), hp = __builtin_amdgcn_readfirstlane(tt >> 6), cp = tt & 63;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const float4* src = (const float4*)&lds[cp * QS + kap(hp, s) * 16];
@@ -366,7 +393,6 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         }
       }
     }
-    __syncthreads();
   }
   // ---------------------------------------------------------------- C2, product, X
   // C2 thread: hp = t / 64 (the pair of c values, uniform per wave), cp = t % 64
@@ -377,7 +403,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   // every wave: its two real columns' products go to LDS and out by all
   // threads.
   {
-    const int hp = t >> 6, cp = t & 63;
+    const int tt = fresh(t), hp = __builtin_amdgcn_readfirstlane(tt >> 6), cp = tt & 63;
     const gcf2 R = (gcf2)desc.rspec;
     float2* Xf = g.X + (size_t)f * N * H;
 #pragma unroll
@@ -393,6 +419,10 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
       }
       const int col = cp + 64 * i;
       const bool packed = i == 0 && cp == 0;
+      // byte offset of element e (ky = kap(hp, e / 16) + 16 (e mod 16), this
+      // column) in a spectrum: 32 bits beside a scalar base
+      const unsigned o0 = (unsigned)(kap(hp, 0) * H + col) * 8u, o1 = (unsigned)(kap(hp, 1) * H + col) * 8u;
+      auto off = [&](int e) { return (e >> 4 ? o1 : o0) + (unsigned)(16 * (e & 15) * H) * 8u; };
       if (packed) {
         // P = F0 + i F128 with F0, F128 the spectra of the real columns 0 and
         // N/2: F0[ky] = (P[ky] + conj P[-ky]) / 2, F128 = (P[ky] - conj P[-ky]) / 2i;
@@ -460,8 +490,8 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         auto load = [&](int b, float2* dst) {
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
-            const int e = 8 * b + k, ky = kap(hp, e >> 4) + 16 * (e & 15);
-            dst[k] = ld2(R + (size_t)ky * H + col);
+            const int e = 8 * b + k;
+            dst[k] = ld2((gcf2)((gcc)R + off(e)));
           }
         };
         load(0, rb[0]);
@@ -476,9 +506,8 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
         }
 #pragma unroll
         for (int e = 0; e < 32; ++e) {
-          const int ky = kap(hp, e >> 4) + 16 * (e & 15);
           const float2 x = r[pslot(e, i)];
-          Xf[(size_t)ky * H + col] = x;
+          *(float2*)((char*)Xf + off(e)) = x;
         }
       }
       if (i == 0) {
@@ -508,7 +537,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   for (int h = 0; h < 2; ++h) {
     __syncthreads();
     {
-      const int hp = t >> 6, cp = t & 63;
+      const int tt = fresh(t), hp = __builtin_amdgcn_readfirstlane(tt >> 6), cp = tt & 63;
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
         const int c = kap(hp, s);
@@ -518,7 +547,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
     }
     __syncthreads();
     {
-      const int ap = t & 15, cq = t >> 4;
+      const int tt = fresh(t), ap = tt & 15, cq = tt >> 4;
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii) {
         const int cl = cq + 32 * ii;
@@ -547,7 +576,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   for (int h = 0; h < 2; ++h) {
     __syncthreads();
     {
-      const int ap = t & 15, cq = t >> 4;
+      const int tt = fresh(t), ap = tt & 15, cq = tt >> 4;
 #pragma unroll
       for (int ii = 0; ii < 2; ++ii) {
         const int cl = cq + 32 * ii;
@@ -557,7 +586,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
     }
     __syncthreads();
     {
-      const int gg = t & 7, rq = t >> 3;
+      const int tt = fresh(t), gg = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
@@ -571,7 +600,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   }
   // ---------------------------------------------------------------- pack + J1
   {
-    const int gg = t & 7;
+    const int tt = fresh(t), gg = tt & 7;
     float2 w[16];
 #pragma unroll
     for (int s = 0; s < 2; ++s)
@@ -618,9 +647,12 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
   // J2 thread: a'' = t % 8, rq = t / 8
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    __syncthreads();
+    if (h == 0)
+      __syncthreads();  // (then a wave's rows are its own, as in E2)
+    else
+      wave_order();
     {
-      const int gg = t & 7, rq = t >> 3;
+      const int tt = fresh(t), gg = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int j = 2 * h + jj, yl = rq + 64 * jj;
@@ -630,9 +662,9 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
           for (int a = 0; a < 8; ++a) lds[yl * RS7 + e7pos(a, kap(gg, s))] = r[j * 16 + s * 8 + a];
       }
     }
-    __syncthreads();
+    wave_order();
     {
-      const int a2 = t & 7, rq = t >> 3;
+      const int tt = fresh(t), a2 = tt & 7, rq = tt >> 3;
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int j = 2 * h + jj, yl = rq + 64 * jj;
@@ -666,6 +698,7 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
       }
     }
   }
+  const float mine = t1;
   auto merge2 = [](float& a1, float& a2, float b1, float b2) {
     const float lo = fminf(a1, b1);
     a1 = fmaxf(a1, b1);
@@ -691,8 +724,8 @@ __global__ void __launch_bounds__(kT) k_xcorr256(GroupParams g) {
 #pragma unroll
   for (int w = 1; w < kT / 64; ++w) merge2(t1, t2, redf[0][w], redf[1][w]);
   unsigned idx = 0xFFFFFFFFu;
-  {
-    const int a2 = t & 7, rq = t >> 3;
+  if (mine == t1) {  // (few threads hold the maximum)
+    const int tt = fresh(t), a2 = tt & 7, rq = tt >> 3;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll

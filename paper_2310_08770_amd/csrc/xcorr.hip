@@ -29,9 +29,9 @@ constexpr int rows_per_block(int NY, int NX, int budget) {
   return best;
 }
 
-// columns per block of the column pass: at most 2048 complex values per
-// LDS buffer (8 columns of 256: 37 KB of LDS, so four blocks share a CU),
-// no wider than the NX/2+1 columns need
+// columns per block of the column pass: at most 2048 complex values in LDS
+// (8 columns of 256: 21 KB, so the four blocks of a CU's 32 waves fit), no
+// wider than the NX/2+1 columns need
 constexpr int cols_per_block(int NY, int NX) {
   int cb = 1;
   while (cb * 2 * NY <= 2048 && cb < NX / 2) cb *= 2;
@@ -130,8 +130,7 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
   constexpr int LS = lds_len(L) + 1;  // row stride in LDS
   const R eps = (R)eps_in;
   __shared__ C tw[NX];
-  __shared__ C bufA[RPB * LS];
-  __shared__ C bufB[RPB * LS];
+  __shared__ C buf[RPB * LS];
   __shared__ unsigned red[3][kThreads / 64];
   const unsigned tid = threadIdx.x;
   const int f = blockIdx.y;
@@ -162,14 +161,14 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
       const unsigned w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e)
-        bufA[r * LS + lds_idx(4 * q + e)] = mkc<C>(pro((R)(w[e] & 0xFFFFu)), pro((R)(w[e] >> 16)));
+        buf[r * LS + lds_idx(4 * q + e)] = mkc<C>(pro((R)(w[e] & 0xFFFFu)), pro((R)(w[e] >> 16)));
     }
   } else if (vec32) {
     for (unsigned i = tid; i < (unsigned)(RPB * (NX / 4)); i += kThreads) {
       const unsigned r = i / (NX / 4), q = i % (NX / 4);
       const float4 v = *(const float4*)((const float*)data + (long)(y0 + r) * pitch + 4 * q);
-      bufA[r * LS + lds_idx(2 * q)] = mkc<C>(pro((R)v.x), pro((R)v.y));
-      bufA[r * LS + lds_idx(2 * q + 1)] = mkc<C>(pro((R)v.z), pro((R)v.w));
+      buf[r * LS + lds_idx(2 * q)] = mkc<C>(pro((R)v.x), pro((R)v.y));
+      buf[r * LS + lds_idx(2 * q + 1)] = mkc<C>(pro((R)v.z), pro((R)v.w));
     }
   } else if (trans) {
     // row y of the tall image is column y of the wide frame: adjacent threads
@@ -179,7 +178,7 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
       const long idx = (long)(2 * c) * pitch + (y0 + r);
       const R a0 = pro(load_px<R>(data, dtype, idx));
       const R a1 = pro(load_px<R>(data, dtype, idx + pitch));
-      bufA[r * LS + lds_idx(c)] = mkc<C>(a0, a1);
+      buf[r * LS + lds_idx(c)] = mkc<C>(a0, a1);
     }
   } else {
     for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
@@ -187,7 +186,7 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
       const long idx = (long)(y0 + r) * pitch + 2 * c;
       const R a0 = pro(load_px<R>(data, dtype, idx));
       const R a1 = pro(load_px<R>(data, dtype, idx + 1));
-      bufA[r * LS + lds_idx(c)] = mkc<C>(a0, a1);
+      buf[r * LS + lds_idx(c)] = mkc<C>(a0, a1);
     }
   }
   if (st) {
@@ -211,7 +210,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
     atomicMax(&st[f].amax, kmax);
     if (bad) atomicOr(&st[f].flags, (unsigned)CCPT_ST_NONFINITE);
   }
-  C* z = fft_lds<L, -1, NX>(bufA, bufB, RPB, LS, tw);
+  fft_lds<L, -1, NX, RPB, kThreads>(buf, RPB, LS, tw);
+  const C* z = buf;
   // unpack: X[k] = E[k] + W^k O[k], E = (Z[k] + conj Z[L-k]) / 2,
   // O = (Z[k] - conj Z[L-k]) / (2i), W = exp(-2 pi i / NX); stored column-major
   // T[k][y] so each column k receives RPB consecutive rows
@@ -246,8 +246,7 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
   constexpr int CS = CB + 1;  // column slots: CB regular + the Nyquist slot of block 0
   const C zero = mkc<C>(0, 0);
   __shared__ C tw[NY];
-  __shared__ C bufA[CS * S];
-  __shared__ C bufB[CS * S];
+  __shared__ C buf[CS * S];
   const unsigned tid = threadIdx.x;
   const int f = blockIdx.y;
   const int c0 = blockIdx.x * CB;
@@ -286,7 +285,7 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
       row_of(i, y, c);
       if (i < count) {
         const bool ok = col_of(c) >= 0;
-        bufA[c * S + lds_idx(y)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
+        buf[c * S + lds_idx(y)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
       }
     }
   } else {
@@ -311,20 +310,22 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
       const unsigned i = tid + it * kThreads;
       if (i < count) {
         const bool ok = col_of(i / NY) >= 0;
-        bufA[i / NY * S + lds_idx(i % NY)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
+        buf[i / NY * S + lds_idx(i % NY)] = mkc<C>(ok ? in[it].x : 0, ok ? in[it].y : 0);
       }
     }
   }
   __syncthreads();
   if constexpr (KIND == COL_INV) {
-    C* r = fft_lds<NY, +1, NY>(bufA, bufB, nseq, S, tw);
+    fft_lds<NY, +1, NY, CS, kThreads>(buf, nseq, S, tw);
+    const C* r = buf;
     for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
       const unsigned c = i / NY, y = i % NY;
       const int kx = col_of(c);
       if (kx >= 0) Tf[(size_t)kx * NY + y] = r[c * S + lds_idx(y)];
     }
   } else {
-    C* r = fft_lds<NY, -1, NY>(bufA, bufB, nseq, S, tw);
+    fft_lds<NY, -1, NY, CS, kThreads>(buf, nseq, S, tw);
+    C* r = buf;
     if constexpr (KIND == COL_FWD || KIND == COL_FWD_CONJ) {
       C* out = spec + (size_t)f * spec_stride;
       for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
@@ -354,8 +355,8 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
         }
       }
       __syncthreads();
-      C* o = (r == bufA) ? bufB : bufA;
-      C* q = fft_lds<NY, +1, NY>(r, o, nseq, S, tw);
+      fft_lds<NY, +1, NY, CS, kThreads>(buf, nseq, S, tw);
+      const C* q = buf;
       for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
         const unsigned c = i / NY, y = i % NY;
         const int kx = col_of(c);
@@ -384,10 +385,8 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   constexpr int L = NX / 2, H = NX / 2 + 1;
   constexpr int LS = lds_len(L) + 1;
   __shared__ C tw[NX];
-  __shared__ C bufA[RPB * LS];
-  __shared__ C bufB[RPB * LS];
-  static_assert(LS >= H, "bins fit bufB");
-  C* const raw = bufB;  // the bins as read, until they are packed into bufA
+  __shared__ C buf[RPB * LS];
+  static_assert(LS >= H, "a row's bins fit its sequence");
   __shared__ float redf[2][kThreads / 64];
   __shared__ unsigned redu[kThreads / 64];
   __shared__ double redv[kThreads / 64], redv2[kThreads / 64];
@@ -409,7 +408,7 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
       const unsigned i = tid + it * kThreads;
-      if ((RPB * H) % kThreads == 0 || i < (unsigned)(RPB * H)) raw[i % RPB * H + i / RPB] = in[it];
+      if ((RPB * H) % kThreads == 0 || i < (unsigned)(RPB * H)) buf[i % RPB * LS + i / RPB] = in[it];
     }
   }
   // frame row-major index of tall pixel (y, x), and the step to (y, x + 1)
@@ -420,16 +419,29 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   const unsigned xstep = trans ? (unsigned)NY : 1u;
   __syncthreads();
   const R half = R(0.5);
-  for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
-    const unsigned r = i / L, k = i % L;
-    const C xk = raw[r * H + k];
-    const C xc = cconj(raw[r * H + L - k]);
-    const C e = cscale(cadd(xk, xc), half);
-    const C o = cmul(cscale(csub(xk, xc), half), cconj(tw[k]));
-    bufA[r * LS + lds_idx(k)] = mkc<C>(e.x - o.y, e.y + o.x);  // e + i o
+  {
+    constexpr int IT = (RPB * L + kThreads - 1) / kThreads;
+    C zp[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * L - 1));
+      const unsigned r = i / L, k = i % L;
+      const C xk = buf[r * LS + k];
+      const C xc = cconj(buf[r * LS + L - k]);
+      const C e = cscale(cadd(xk, xc), half);
+      const C o = cmul(cscale(csub(xk, xc), half), cconj(tw[k]));
+      zp[it] = mkc<C>(e.x - o.y, e.y + o.x);  // e + i o
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      if ((RPB * L) % kThreads == 0 || i < (unsigned)(RPB * L)) buf[i / L * LS + lds_idx(i % L)] = zp[it];
+    }
   }
   __syncthreads();
-  C* z = fft_lds<L, +1, NX>(bufA, bufB, RPB, LS, tw);
+  fft_lds<L, +1, NX, RPB, kThreads>(buf, RPB, LS, tw);
+  const C* z = buf;
   if constexpr (ARGMAX && !FP64) {
     // the two largest values of the block (equal ones count twice), then the
     // lowest frame row-major index that holds the largest

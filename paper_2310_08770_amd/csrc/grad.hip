@@ -90,7 +90,8 @@ __global__ void __launch_bounds__(kGThreads) k_grad_psi(const FrameDesc* __restr
   const double inv = 1.0 / ((double)N * (double)N);
   const size_t base = (size_t)f * N * H;
   const float2* R = (const float2*)d.rspec;
-  for (int i = tid; i < rows * H; i += kGThreads) {
+  const int mine = min(rows, N - y0);  // (the last block of a size that 8 does not divide)
+  for (int i = tid; i < mine * H; i += kGThreads) {
     const int ky = y0 + i / H, kx = i % H;
     const size_t e = (size_t)ky * H + kx;
     float2 qa = make_float2(0.f, 0.f), qb = qa;
@@ -243,7 +244,7 @@ static int grad_psi_n(const FrameDesc* desc, int first, int count, const ccpt_re
                       const double* g_d, const double* g_peak, const float2* FA, float2* QA,
                       float2* QB, hipStream_t s) {
   const int rows = N >= 64 ? 8 : N;
-  hipLaunchKernelGGL((k_grad_psi<N>), dim3(N / rows, count), dim3(kGThreads), 0, s, desc, first,
+  hipLaunchKernelGGL((k_grad_psi<N>), dim3((N + rows - 1) / rows, count), dim3(kGThreads), 0, s, desc, first,
                      fwd, g_d, g_peak, FA, QA, QB, rows);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }

@@ -1133,7 +1133,45 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
     img_need = std::max(img_need, per_frame(ctx->refs[r].n) + 256);
   rc = ensure_ws(ctx, std::max(ws_need, img_need));
   if (rc) return rc;
-  const size_t small_bytes = (size_t)n * sizeof(long) + (size_t)nrefs * sizeof(void*);
+  // frames of each chunk by reference, in runs (the sums of the reference gradients)
+  struct ChunkSums {
+    int order, run, nruns, head, nheads;
+  };
+  std::vector<int> order;
+  std::vector<int2> runs;
+  std::vector<int4> heads;
+  std::vector<ChunkSums> sums;
+  if (g_ref) {
+    int first = 0;
+    for (size_t gi = 0; gi < plan.sig.size(); gi += 2) {
+      const int nn = plan.sig[gi], cnt = plan.sig[gi + 1];
+      const int chunk = std::max(1, std::min<int>(cnt, (int)(budget / per_frame(nn))));
+      for (int c0 = 0; c0 < cnt; c0 += chunk) {
+        const int count = std::min(chunk, cnt - c0);
+        const FrameDesc* d = plan.desc.data() + first + c0;
+        ChunkSums cs{(int)order.size(), (int)runs.size(), 0, (int)heads.size(), 0};
+        for (int i = 0; i < count; ++i) order.push_back(i);
+        int* o = order.data() + cs.order;
+        std::stable_sort(o, o + count, [&](int x, int y) { return d[x].ref_id < d[y].ref_id; });
+        for (int i = 0; i < count;) {
+          const int ref = d[o[i]].ref_id, run0 = (int)runs.size() - cs.run;
+          int e = i;
+          while (e < count && d[o[e]].ref_id == ref) ++e;
+          for (; i < e; i += kSumRun) runs.push_back(int2{i, std::min(kSumRun, e - i)});
+          i = e;
+          heads.push_back(int4{ref, run0, (int)runs.size() - cs.run - run0, 0});
+        }
+        cs.nruns = (int)runs.size() - cs.run;
+        cs.nheads = (int)heads.size() - cs.head;
+        sums.push_back(cs);
+      }
+      first += cnt;
+    }
+  }
+  // the small tables, in order of alignment
+  const size_t o_runs = heads.size() * sizeof(int4), o_goff = o_runs + runs.size() * sizeof(int2);
+  const size_t o_acc = o_goff + (size_t)n * sizeof(long), o_order = o_acc + (size_t)nrefs * sizeof(void*);
+  const size_t small_bytes = o_order + order.size() * sizeof(int);
   rc = ensure_buf(ctx, ctx->gsmall, ctx->gsmall_cap, small_bytes);
   if (rc) return rc;
   if (g_ref) {
@@ -1152,21 +1190,27 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
       return fail(ctx, CCPT_E_NOMEM, "pinned staging");
     ctx->h_small_cap = small_bytes;
   }
-  memcpy(ctx->h_small, goff.data(), (size_t)n * sizeof(long));
-  float2** accp = (float2**)(ctx->h_small + (size_t)n * sizeof(long));
+  if (g_ref) {
+    memcpy(ctx->h_small, heads.data(), heads.size() * sizeof(int4));
+    memcpy(ctx->h_small + o_runs, runs.data(), runs.size() * sizeof(int2));
+    memcpy(ctx->h_small + o_order, order.data(), order.size() * sizeof(int));
+  }
+  memcpy(ctx->h_small + o_goff, goff.data(), (size_t)n * sizeof(long));
+  float2** accp = (float2**)(ctx->h_small + o_acc);
   for (int r = 0; r < nrefs; ++r)
     accp[r] = g_ref ? (float2*)ctx->acc_buf + aoff[r] : nullptr;
   HIP_CHECK(ctx, hipMemcpyAsync(ctx->gsmall, ctx->h_small, small_bytes, hipMemcpyHostToDevice, s));
   HIP_CHECK(ctx, hipEventRecord(ctx->small_evt, s));
-  const long* d_goff = (const long*)ctx->gsmall;
-  float2* const* d_acc = (float2* const*)((char*)ctx->gsmall + (size_t)n * sizeof(long));
+  const char* small = (const char*)ctx->gsmall;
+  const long* d_goff = (const long*)(small + o_goff);
+  float2* const* d_acc = (float2* const*)(small + o_acc);
   if (g_ref && launch_zero(ctx->acc_buf, (size_t)ao * sizeof(float2), s))
     return fail(ctx, CCPT_E_HIP, "zero launch failed");
 
   const Marker mark = marker_of(ctx, s);
   const int mode = ctx->o.mode;
   const float eps = (float)ctx->o.eps;
-  int first = 0;
+  int first = 0, chunk_no = 0;
   mark(CCPT_STAGE_GRAD, 1);
   for (size_t gi = 0; gi < plan.sig.size(); gi += 2) {
     const int nn = plan.sig[gi], cnt = plan.sig[gi + 1];
@@ -1181,16 +1225,30 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
       float2* QB = QA + spec * chunk;
       float* img = (float*)(QB + spec * chunk);
       const int f0 = first + c0;
-      if (launch_frame_spectra(nn, nn, 0, ctx->d_desc, f0, count, mode, eps, T, FA, tw, s) ||
-          launch_grad_psi(nn, ctx->d_desc, f0, count, fwd, g_d, g_peak, FA, QA,
-                          g_ref ? QB : nullptr, s))
-        return fail(ctx, CCPT_E_HIP, "gradient launch failed");
-      if (g_frames && (launch_inverse(nn, nn, QA, count, 2.0f, T, img, tw, s) ||
-                       launch_grad_frames(nn, ctx->d_desc, f0, count, img, d_goff, g_frames, mode,
-                                          eps, s)))
-        return fail(ctx, CCPT_E_HIP, "frame gradient launch failed");
-      if (g_ref && launch_ref_accum(nn, ctx->d_desc, f0, count, QB, d_acc, s))
-        return fail(ctx, CCPT_E_HIP, "reference gradient launch failed");
+      GradParams g{ctx->d_desc, f0, count, fwd, g_d, g_peak, g_ref ? QB : nullptr, d_goff, g_frames, mode, eps, tw};
+      // frames that fit LDS in one kernel, the others in passes
+      const int nl = lds_frames(nn, nn, count, kGradMinFrames);
+      g.count = nl;
+      if (nl > 0 && launch_grad_lds(nn, g, s)) return fail(ctx, CCPT_E_HIP, "gradient launch failed");
+      if (nl < count) {
+        g.first = f0 + nl;
+        g.count = count - nl;
+        if (g_ref) g.QB = QB + spec * nl;
+        if ((g_ref && launch_frame_spectra(nn, nn, 0, ctx->d_desc, g.first, g.count, mode, eps, T, FA, tw, s)) ||
+            launch_grad_psi(nn, g, FA, QA, s))
+          return fail(ctx, CCPT_E_HIP, "gradient launch failed");
+        if (g_frames && (launch_inverse(nn, nn, QA, g.count, 2.0f, T, img, tw, s) ||
+                         launch_grad_frames(nn, ctx->d_desc, g.first, g.count, img, d_goff, g_frames, mode,
+                                            eps, s)))
+          return fail(ctx, CCPT_E_HIP, "frame gradient launch failed");
+      }
+      if (g_ref) {
+        const ChunkSums& cs = sums[chunk_no++];
+        const RefSums t{(const int*)(small + o_order) + cs.order, (const int2*)(small + o_runs) + cs.run,
+                        (const int4*)small + cs.head, cs.nruns, cs.nheads};
+        if (launch_ref_accum(nn, QB, t, d_acc, s))
+          return fail(ctx, CCPT_E_HIP, "reference gradient launch failed");
+      }
     }
     first += cnt;
   }

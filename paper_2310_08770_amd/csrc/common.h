@@ -231,7 +231,7 @@ inline bool xcorr_fused(int ny, int nx, bool pairs_ok, int count, int fused_min)
 
 // The correlation stage of frames whose half spectrum fits LDS in one kernel,
 // one block per frame (xcorr_lds.hip): the same bits as the three passes.
-// xcorr_lds_frames: how many of a launch's `count` frames, from the first,
+// lds_frames: how many of a launch's `count` frames, from the first,
 // take it.  Frames of at most kLdsSmall half-spectrum values (128 x 128) always
 // do: several blocks share a CU, and even one frame alone is no slower than
 // three launches.  Larger ones have a CU each, so they go in rounds of
@@ -241,7 +241,8 @@ inline bool xcorr_fused(int ny, int nx, bool pairs_ok, int count, int fused_min)
 constexpr int kLdsSmall = 8320;
 constexpr int kLdsRound = 256;
 constexpr int kLdsMinFrames = 128;
-int xcorr_lds_frames(int ny, int nx, int count);
+constexpr int kGradMinFrames = 64;  // the adjoint's launches (grad.hip), in place of kLdsMinFrames
+int lds_frames(int ny, int nx, int count, int min_frames = kLdsMinFrames);
 int launch_xcorr_lds(int ny, int nx, const GroupParams& g, hipStream_t s);
 
 // FP64 mode: the same two calls with every FFT in FP64 (g.T64, g.X64,
@@ -286,14 +287,38 @@ int launch_frame_spectra(int ny, int nx, int trans, const FrameDesc* desc, int f
                          int mode, float eps, float2* T, float2* spec, const float2* tw,
                          hipStream_t s);
 
-// Adjoint pieces (grad.hip).
-int launch_grad_psi(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd,
-                    const double* g_d, const double* g_peak, const float2* FA, float2* QA,
-                    float2* QB, hipStream_t s);
+// Adjoint (grad.hip).  Parameters of a launch over frames [first, first + count)
+// of the descriptors; QB (or null) and the products are indexed from `first`.
+struct GradParams {
+  const FrameDesc* desc;
+  int first, count;
+  const ccpt_result* fwd;
+  const double* g_d;
+  const double* g_peak;  // or null
+  float2* QB;            // [count][N][N/2+1] spectra of the reference gradient, or null
+  const long* goff;      // frame gradient offsets by result index
+  float* g_frames;       // or null
+  int mode;
+  float eps;
+  const float2* tw;
+};
+// Frames that fit LDS: everything but the sum over frames, in one kernel.
+int launch_grad_lds(int N, const GradParams& g, hipStream_t s);
+// From frame spectra FA: QA (frame gradient) and g.QB.
+int launch_grad_psi(int N, const GradParams& g, const float2* FA, float2* QA, hipStream_t s);
 int launch_grad_frames(int N, const FrameDesc* desc, int first, int count, const float* img,
                        const long* goff, float* g_frames, int mode, float eps, hipStream_t s);
-int launch_ref_accum(int N, const FrameDesc* desc, int first, int count, const float2* QB,
-                     float2* const* acc, hipStream_t s);
+// Sums of a chunk's QB by reference: order lists the chunk's frames, each
+// reference's together and ascending; runs = (start in order, frames, at most
+// kSumRun) of one reference each; heads = (reference, first run, runs).
+constexpr int kSumRun = 16;
+struct RefSums {
+  const int* order;
+  const int2* runs;
+  const int4* heads;
+  int nruns, nheads;
+};
+int launch_ref_accum(int N, float2* QB, const RefSums& t, float2* const* acc, hipStream_t s);
 int launch_grad_ref_chain(const float* img, const float* E, int nn, int mode, float eps,
                           float* out, hipStream_t s);
 int launch_fisher_deriv(int N, const float2* F, float2* Dy, float2* Dx, hipStream_t s);

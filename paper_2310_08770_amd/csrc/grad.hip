@@ -23,7 +23,7 @@
 #include <math.h>
 
 #include "common.h"
-#include "fft.h"
+#include "lds_frame.h"
 
 namespace ccpt {
 
@@ -55,8 +55,46 @@ __device__ __forceinline__ bool grad_usable(unsigned status) {
                     CCPT_ST_WINDOW_EXIT)) == 0;
 }
 
+// Psi of one frame: lam, the cotangent of C(d), and the phases of d.  With
+// u = (g_c phi_kx + lam_x phi'_kx) / N^2 and v = lam_y phi_kx / N^2,
+// Psi(ky, kx) = phi_ky u + phi'_ky v.
+struct Adjoint {
+  double lam_y, lam_x, gc;
+  bool ok;
+};
+
+__device__ __forceinline__ Adjoint adjoint_of(const ccpt_result& r, int out_idx, const double* __restrict__ g_d,
+                                              const double* __restrict__ g_peak) {
+  Adjoint a{0.0, 0.0, 0.0, grad_usable(r.status)};
+  if (a.ok) {
+    const double gy = g_d[2 * out_idx], gx = g_d[2 * out_idx + 1];
+    const double hyy = r.hess[0], hyx = r.hess[1], hxx = r.hess[2];
+    const double det = hyy * hxx - hyx * hyx;
+    // lam = -H^-1 g
+    a.lam_y = -(hxx * gy - hyx * gx) / det;
+    a.lam_x = -(hyy * gx - hyx * gy) / det;
+    a.gc = g_peak ? g_peak[out_idx] : 0.0;
+  }
+  return a;
+}
+
+__device__ __forceinline__ void col_factors(int k, int n, double s, const Adjoint& a, double2& u, double2& v) {
+  double2 p, dp;
+  phi2(k, n, s, p, dp);
+  const double inv = 1.0 / ((double)n * (double)n);
+  u = make_double2((a.gc * p.x + a.lam_x * dp.x) * inv, (a.gc * p.y + a.lam_x * dp.y) * inv);
+  v = make_double2(a.lam_y * p.x * inv, a.lam_y * p.y * inv);
+}
+
+__device__ __forceinline__ double2 psi_of(double2 py, double2 dpy, double2 u, double2 v) {
+  const double2 a = zmul(py, u), b = zmul(dpy, v);
+  return make_double2(a.x + b.x, a.y + b.y);
+}
+
 // One block per (ky block, frame): builds Psi on the half spectrum and writes
 // QA = conj(R Psi) (frame gradient) and QB = F[A] Psi (reference gradient).
+constexpr int kPsiRows = 16;
+
 template <int N>
 __global__ void __launch_bounds__(kGThreads) k_grad_psi(const FrameDesc* __restrict__ desc, int first,
                                                         const ccpt_result* __restrict__ fwd,
@@ -64,52 +102,124 @@ __global__ void __launch_bounds__(kGThreads) k_grad_psi(const FrameDesc* __restr
                                                         const double* __restrict__ g_peak,
                                                         const float2* __restrict__ FA,
                                                         float2* __restrict__ QA,
-                                                        float2* __restrict__ QB, int rows) {
+                                                        float2* __restrict__ QB) {
   constexpr int H = N / 2 + 1;
-  __shared__ double2 ey0[N], ey1[N];
-  __shared__ double2 ex0[H], ex1[H];
+  __shared__ double2 ey0[kPsiRows], ey1[kPsiRows];
+  __shared__ double2 ux[H], vx[H];
   const int tid = threadIdx.x;
   const int f = blockIdx.y;
-  const int y0 = blockIdx.x * rows;
+  const int y0 = blockIdx.x * kPsiRows;
+  const int rows = min(kPsiRows, N - y0);
   const FrameDesc d = desc[first + f];
   const ccpt_result r = fwd[d.out_idx];
-  double lam_y = 0.0, lam_x = 0.0, gc = 0.0;
-  const bool ok = grad_usable(r.status);
-  if (ok) {
-    const double gy = g_d[2 * d.out_idx], gx = g_d[2 * d.out_idx + 1];
-    const double hyy = r.hess[0], hyx = r.hess[1], hxx = r.hess[2];
-    const double det = hyy * hxx - hyx * hyx;
-    // lam = -H^-1 g
-    lam_y = -(hxx * gy - hyx * gx) / det;
-    lam_x = -(hyy * gx - hyx * gy) / det;
-    gc = g_peak ? g_peak[d.out_idx] : 0.0;
-  }
-  for (int k = tid; k < N; k += kGThreads) phi2(k, N, r.d[0], ey0[k], ey1[k]);
-  for (int k = tid; k < H; k += kGThreads) phi2(k, N, r.d[1], ex0[k], ex1[k]);
+  const Adjoint ad = adjoint_of(r, d.out_idx, g_d, g_peak);
+  for (int k = tid; k < rows; k += kGThreads) phi2(y0 + k, N, r.d[0], ey0[k], ey1[k]);
+  for (int k = tid; k < H; k += kGThreads) col_factors(k, N, r.d[1], ad, ux[k], vx[k]);
   __syncthreads();
-  const double inv = 1.0 / ((double)N * (double)N);
   const size_t base = (size_t)f * N * H;
   const float2* R = (const float2*)d.rspec;
-  const int mine = min(rows, N - y0);  // (the last block of a size that 8 does not divide)
-  for (int i = tid; i < mine * H; i += kGThreads) {
-    const int ky = y0 + i / H, kx = i % H;
-    const size_t e = (size_t)ky * H + kx;
+  for (int i = tid; i < rows * H; i += kGThreads) {
+    const int ry = i / H, kx = i % H;
+    const size_t e = (size_t)(y0 + ry) * H + kx;
     float2 qa = make_float2(0.f, 0.f), qb = qa;
-    if (ok) {
-      const double2 py = ey0[ky], dpy = ey1[ky], px = ex0[kx], dpx = ex1[kx];
-      double2 psi = zmul(py, px);
-      const double2 a = zmul(dpy, px), b = zmul(py, dpx);
-      psi = make_double2((gc * psi.x + lam_y * a.x + lam_x * b.x) * inv,
-                         (gc * psi.y + lam_y * a.y + lam_x * b.y) * inv);
+    if (ad.ok) {
+      const double2 psi = psi_of(ey0[ry], ey1[ry], ux[kx], vx[kx]);
       const float2 rr = R[e];
       const double2 ra = zmul(make_double2(rr.x, rr.y), psi);
       qa = make_float2((float)ra.x, (float)-ra.y);
-      const float2 fa = FA[base + e];
-      const double2 rb = zmul(make_double2(fa.x, fa.y), psi);
-      qb = make_float2((float)rb.x, (float)rb.y);
+      if (QB) {
+        const float2 fa = FA[base + e];
+        const double2 rb = zmul(make_double2(fa.x, fa.y), psi);
+        qb = make_float2((float)rb.x, (float)rb.y);
+      }
     }
     QA[base + e] = qa;
     if (QB) QB[base + e] = qb;
+  }
+}
+
+// The whole adjoint of a frame that fits LDS, one block per frame: F[A], the
+// product with Psi (QB to memory for the reference gradient, QA back into
+// LDS), and the inverse transform times the chain factor to the caller's
+// gradient array.  Memory sees the frame, the reference spectrum, QB and the
+// gradient once; the passes (spectra, k_grad_psi, inverse, k_grad_frames) move
+// eight spectra more per frame.  Bound as k_xcorr_lds by VALU issue and LDS.
+// 1024 frames of 128 x 128: 233 us -> 110.  Larger frames than kLdsSmall have a
+// CU each, so a last round of few goes to the passes: whole adjoint at 192 x
+// 192, passes / one kernel, 8 frames 57 / 78 us, 64 frames 80 / 86, 128 frames
+// 106 / 90; at 144 x 144 58 / 60, 76 / 65, 90 / 69 (kGradMinFrames lies
+// between); at 128 x 128 one frame takes 52 / 50.
+template <int N>
+__global__ void __launch_bounds__(lds::lds_threads(N, N)) k_grad_lds(GradParams g) {
+  using namespace lds;
+  constexpr int THR = lds_threads(N, N), L = N / 2, H = L + 1, S = Col<N>::S;
+  __shared__ float2 m[H * S];
+  __shared__ float2 tw[N];
+  __shared__ double2 ey0[N], ey1[N];
+  __shared__ double2 ux[H], vx[H];
+  const int f = blockIdx.x;
+  const FrameDesc d = g.desc[g.first + f];
+  const ccpt_result& r = g.fwd[d.out_idx];
+  const Adjoint ad = adjoint_of(r, d.out_idx, g.g_d, g.g_peak);
+  const bool sn = g.mode == CCPT_MODE_CCSN;
+  for (int i = threadIdx.x; i < N; i += THR) tw[i] = g.tw[i];
+  unsigned kmin, kmax, bad;
+  load_frame<N, N, THR>(d, sn, g.eps, false, m, kmin, kmax, bad);
+  for (int k = threadIdx.x; k < N + H; k += THR) {
+    if (k < N)
+      phi2(k, N, r.d[0], ey0[k], ey1[k]);
+    else
+      col_factors(k - N, N, r.d[1], ad, ux[k - N], vx[k - N]);
+  }
+  __syncthreads();
+  if (g.QB) {
+    rows_forward<N, N, THR>(m, tw, g.tw);
+    stages<N, -1, H, N, N, false, THR, false, 0, 1>(m, tw, g.tw, NoUse());
+  }
+  {
+    const float2* R = (const float2*)d.rspec;
+    constexpr int BT = 4;  // reference values in flight per thread
+    for (unsigned i0 = fresh_tid(); i0 < N * H; i0 += BT * THR) {
+      float2 rr[BT];
+#pragma unroll
+      for (int e = 0; e < BT; ++e) rr[e] = R[min(i0 + e * THR, (unsigned)(N * H - 1))];
+#pragma unroll
+      for (int e = 0; e < BT; ++e) {
+        const unsigned i = i0 + e * THR;
+        if (i < N * H) {
+          const unsigned y = i / H, kx = i % H, a = at<N, false>(kx, y);
+          float2 qa = make_float2(0.f, 0.f), qb = qa;
+          if (ad.ok) {
+            const double2 psi = psi_of(ey0[y], ey1[y], ux[kx], vx[kx]);
+            const double2 ra = zmul(make_double2(rr[e].x, rr[e].y), psi);
+            qa = make_float2((float)ra.x, (float)-ra.y);
+            const float2 fa = m[a];
+            const double2 rb = zmul(make_double2(fa.x, fa.y), psi);
+            qb = make_float2((float)rb.x, (float)rb.y);
+          }
+          m[a] = qa;
+          if (g.QB) g.QB[(size_t)f * N * H + i] = qb;
+        }
+      }
+    }
+  }
+  if (!g.g_frames) return;
+  __syncthreads();
+  stages<N, +1, H, N, N, false, THR, false, 0, 1>(m, tw, g.tw, NoUse());
+  pack_rows<N, N, THR>(m, tw);
+  stages<L, +1, N, N, N, true, THR, false, 0, 1>(m, tw, g.tw, NoUse());
+  float* out = g.g_frames + g.goff[d.out_idx];
+  for (unsigned i = fresh_tid(); i < N * L; i += THR) {
+    const unsigned y = i / L, n = i % L;
+    float2 v = m[at<N, true>(y, n)];
+    v = make_float2(2.0f * v.x, 2.0f * v.y);  // the scale of the packed inverse
+    if (sn) {
+      const long idx = (long)y * d.pitch + 2 * n;
+      v.x *= 2.0f * (lds::load_px(d.data, d.dtype, idx) + g.eps);
+      v.y *= 2.0f * (lds::load_px(d.data, d.dtype, idx + 1) + g.eps);
+    }
+    out[2 * i] = v.x;
+    out[2 * i + 1] = v.y;
   }
 }
 
@@ -137,32 +247,49 @@ __global__ void k_grad_frames(const FrameDesc* __restrict__ desc, int first,
   }
 }
 
-// acc[ref][k] += sum over the chunk's frames of that reference of QB[f][k],
-// frames taken in order (deterministic).
+// acc[ref][k] += sum over the chunk's frames of that reference of QB[f][k], in
+// two levels of fixed order: each run of at most kSumRun frames of one
+// reference (order[run.x .. run.x + run.y)) is summed into its first frame's
+// QB, then each reference's runs are summed into acc.  A thread has a run's
+// loads in flight together; one thread per element over all frames waited for
+// each in turn (795 frames of 128 x 128: 338 us -> 26).
 template <int N>
-__global__ void k_ref_accum(const FrameDesc* __restrict__ desc, int first, int count,
-                            const float2* __restrict__ QB, float2* const* __restrict__ acc) {
-  constexpr int H = N / 2 + 1;
+__global__ void k_sum_runs(float2* __restrict__ QB, const int* __restrict__ order,
+                           const int2* __restrict__ runs) {
+  constexpr int NH = N * (N / 2 + 1);
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= N * H) return;
-  int cur = -1;
+  const int2 run = runs[blockIdx.y];
+  if (e >= NH || run.y < 2) return;
+  float2 v[kSumRun];
+#pragma unroll
+  for (int j = 0; j < kSumRun; ++j) v[j] = QB[(size_t)order[run.x + min(j, run.y - 1)] * NH + e];
+  float2 sum = v[0];
+#pragma unroll
+  for (int j = 1; j < kSumRun; ++j)
+    if (j < run.y) sum = cadd(sum, v[j]);
+  QB[(size_t)order[run.x] * NH + e] = sum;
+}
+
+template <int N>
+__global__ void k_sum_refs(const float2* __restrict__ QB, const int* __restrict__ order,
+                           const int2* __restrict__ runs, const int4* __restrict__ heads,
+                           float2* const* __restrict__ acc) {
+  constexpr int NH = N * (N / 2 + 1), BT = 8;
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= NH) return;
+  const int4 h = heads[blockIdx.y];  // reference, first run, runs
   float2 sum = make_float2(0.f, 0.f);
-  for (int f = 0; f < count; ++f) {
-    const int ref = desc[first + f].ref_id;
-    if (ref != cur) {
-      if (cur >= 0) {
-        float2* a = acc[cur];
-        a[e] = cadd(a[e], sum);
-      }
-      cur = ref;
-      sum = make_float2(0.f, 0.f);
-    }
-    sum = cadd(sum, QB[(size_t)f * N * H + e]);
+  for (int r0 = 0; r0 < h.z; r0 += BT) {
+    float2 v[BT];
+#pragma unroll
+    for (int j = 0; j < BT; ++j)
+      v[j] = QB[(size_t)order[runs[h.y + min(r0 + j, h.z - 1)].x] * NH + e];
+#pragma unroll
+    for (int j = 0; j < BT; ++j)
+      if (r0 + j < h.z) sum = cadd(sum, v[j]);
   }
-  if (cur >= 0) {
-    float2* a = acc[cur];
-    a[e] = cadd(a[e], sum);
-  }
+  float2* a = acc[h.x];
+  a[e] = cadd(a[e], sum);
 }
 
 // Reference gradient image: chain factor of B = -1/(E+eps) is 1/(E+eps)^2.
@@ -240,12 +367,9 @@ __global__ void k_fisher_final(const double* __restrict__ part, int nblocks, dou
 // ------------------------------------------------------------ launchers
 
 template <int N>
-static int grad_psi_n(const FrameDesc* desc, int first, int count, const ccpt_result* fwd,
-                      const double* g_d, const double* g_peak, const float2* FA, float2* QA,
-                      float2* QB, hipStream_t s) {
-  const int rows = N >= 64 ? 8 : N;
-  hipLaunchKernelGGL((k_grad_psi<N>), dim3((N + rows - 1) / rows, count), dim3(kGThreads), 0, s, desc, first,
-                     fwd, g_d, g_peak, FA, QA, QB, rows);
+static int grad_psi_n(const GradParams& g, const float2* FA, float2* QA, hipStream_t s) {
+  hipLaunchKernelGGL((k_grad_psi<N>), dim3((N + kPsiRows - 1) / kPsiRows, g.count), dim3(kGThreads), 0, s,
+                     g.desc, g.first, g.fwd, g.g_d, g.g_peak, FA, QA, g.QB);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -258,11 +382,11 @@ static int grad_frames_n(const FrameDesc* desc, int first, int count, const floa
 }
 
 template <int N>
-static int ref_accum_n(const FrameDesc* desc, int first, int count, const float2* QB,
-                       float2* const* acc, hipStream_t s) {
-  constexpr int H = N / 2 + 1;
-  hipLaunchKernelGGL((k_ref_accum<N>), dim3((N * H + 255) / 256), dim3(256), 0, s, desc, first,
-                     count, QB, acc);
+static int ref_accum_n(float2* QB, const RefSums& t, float2* const* acc, hipStream_t s) {
+  constexpr int blocks = (N * (N / 2 + 1) + 255) / 256;
+  hipLaunchKernelGGL((k_sum_runs<N>), dim3(blocks, t.nruns), dim3(256), 0, s, QB, t.order, t.runs);
+  hipLaunchKernelGGL((k_sum_refs<N>), dim3(blocks, t.nheads), dim3(256), 0, s, (const float2*)QB, t.order,
+                     t.runs, t.heads, acc);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -273,16 +397,25 @@ static int fisher_deriv_n(const float2* F, float2* Dy, float2* Dx, hipStream_t s
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_grad_psi(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd,
-                    const double* g_d, const double* g_peak, const float2* FA, float2* QA,
-                    float2* QB, hipStream_t s) {
+int launch_grad_psi(int N, const GradParams& g, const float2* FA, float2* QA, hipStream_t s) {
   switch (N) {
 #define CASE(n) \
   case n:       \
-    return grad_psi_n<n>(desc, first, count, fwd, g_d, g_peak, FA, QA, QB, s);
+    return grad_psi_n<n>(g, FA, QA, s);
     CCPT_FOR_SIZES(CASE)
 #undef CASE
   }
+  return -2;
+}
+
+int launch_grad_lds(int N, const GradParams& g, hipStream_t s) {
+#define CASE(n, n2)                                                                                   \
+  if (N == n) {                                                                                       \
+    hipLaunchKernelGGL((k_grad_lds<n>), dim3(g.count), dim3(lds::lds_threads(n, n)), 0, s, g);         \
+    return hipGetLastError() == hipSuccess ? 0 : -1;                                                  \
+  }
+  CCPT_FOR_LDS_SQUARE(CASE)
+#undef CASE
   return -2;
 }
 
@@ -298,12 +431,11 @@ int launch_grad_frames(int N, const FrameDesc* desc, int first, int count, const
   return -2;
 }
 
-int launch_ref_accum(int N, const FrameDesc* desc, int first, int count, const float2* QB,
-                     float2* const* acc, hipStream_t s) {
+int launch_ref_accum(int N, float2* QB, const RefSums& t, float2* const* acc, hipStream_t s) {
   switch (N) {
 #define CASE(n) \
   case n:       \
-    return ref_accum_n<n>(desc, first, count, QB, acc, s);
+    return ref_accum_n<n>(QB, t, acc, s);
     CCPT_FOR_SIZES(CASE)
 #undef CASE
   }

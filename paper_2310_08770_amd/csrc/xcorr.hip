@@ -660,7 +660,7 @@ int launch_xcorr(int ny, int nx, const GroupParams& g0, hipStream_t s, const Mar
   }
   // (timed launches keep the passes apart, so that each stage has its time; the
   // results are the same)
-  const int nl = mark.fn ? 0 : xcorr_lds_frames(ny, nx, g0.count);
+  const int nl = mark.fn ? 0 : lds_frames(ny, nx, g0.count);
   if (nl > 0) {
     GroupParams a = g0;
     a.count = nl;

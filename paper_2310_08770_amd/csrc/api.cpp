@@ -1351,8 +1351,14 @@ int ccpt_mean_aligned(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_res
   if (launch_zero(acc, head, s)) return fail(ctx, CCPT_E_HIP, "zero launch failed");
   for (int c0 = 0; c0 < n; c0 += chunk) {
     const int count = std::min(chunk, n - c0);
-    if (launch_frame_spectra(N, N, 0, ctx->d_desc, c0, count, CCPT_MODE_CCU, 0.f, T, F, tw, s) ||
-        launch_align_accumulate(N, ctx->d_desc, c0, count, fwd, F, acc, cnt, s))
+    // frames that fit LDS in one kernel, the others in passes
+    const int nl = lds_frames(N, N, count), rest = count - nl;
+    float2* Fr = F + spec * nl;
+    if ((nl > 0 && launch_align_lds(N, ctx->d_desc, c0, nl, fwd, tw, F, cnt, s)) ||
+        (rest > 0 &&
+         (launch_frame_spectra(N, N, 0, ctx->d_desc, c0 + nl, rest, CCPT_MODE_CCU, 0.f, T, Fr, tw, s) ||
+          launch_align(N, ctx->d_desc, c0 + nl, rest, fwd, Fr, cnt, s))) ||
+        launch_sum_spectra(N, count, F, acc, s))
       return fail(ctx, CCPT_E_HIP, "alignment launch failed");
   }
   // the row pass of the inverse returns half the unnormalised transform

@@ -325,13 +325,16 @@ int launch_fisher_deriv(int N, const float2* F, float2* Dy, float2* Dx, hipStrea
 int launch_fisher_reduce(const float* dy, const float* dx, const void* mu, int dtype, int pitch,
                          int n, double* part, int nblocks, double* out, hipStream_t s);
 
-// Offline reference (reference.hip): for a chunk of frames whose spectra
-// are in F ([count][N][N/2+1]), multiplies each by the phases of its
-// displacement (results fwd[desc.out_idx]), adds them in frame order to acc
-// and counts the frames that tracked into cnt.
-int launch_align_accumulate(int N, const FrameDesc* desc, int first, int count,
-                            const ccpt_result* fwd, float2* F, float2* acc, unsigned* cnt,
-                            hipStream_t s);
+// Offline reference (reference.hip).  launch_align: multiplies frame spectra F
+// ([count][N][N/2+1]) by the phases of their displacements (results
+// fwd[desc.out_idx]) and counts the frames that tracked into cnt (the others
+// become zeros); launch_align_lds: the same spectra from the frames themselves,
+// for frames that fit LDS; launch_sum_spectra: adds them in frame order to acc.
+int launch_align(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd, float2* F,
+                 unsigned* cnt, hipStream_t s);
+int launch_align_lds(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd, const float2* tw,
+                     float2* F, unsigned* cnt, hipStream_t s);
+int launch_sum_spectra(int N, int count, const float2* F, float2* acc, hipStream_t s);
 // Real-time reference update of Eq. 9 by one frame (spectrum F, result res):
 // S <- a0 v + b1 S with v the frame shifted back (conjugated when conj_s);
 // spectra held tall, ny x (nx/2+1) (trans: a wide frame, whose shift axes

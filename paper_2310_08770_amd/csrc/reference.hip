@@ -14,7 +14,7 @@
 #include <math.h>
 
 #include "common.h"
-#include "fft.h"
+#include "lds_frame.h"
 
 namespace ccpt {
 
@@ -35,18 +35,20 @@ __device__ __forceinline__ float2 shift_phase(int k, int N, double d) {
 }
 
 // F[f] (row-major N x (N/2+1)) *= phi_ky(d_y) phi_kx(d_x) for frame f's
-// displacement; frames that did not track are zeroed.
+// displacement; frames that did not track are zeroed, the others counted.
 template <int N>
 __global__ void __launch_bounds__(kRefThreads) k_align_spectra(const FrameDesc* __restrict__ desc,
                                                                int first,
                                                                const ccpt_result* __restrict__ fwd,
-                                                               float2* __restrict__ F) {
+                                                               float2* __restrict__ F,
+                                                               unsigned* __restrict__ cnt) {
   constexpr int H = N / 2 + 1;
   __shared__ float2 px[H];
   __shared__ float2 py[kAlignRows];
   const int f = blockIdx.y, y0 = blockIdx.x * kAlignRows, tid = threadIdx.x;
   const ccpt_result r = fwd[desc[first + f].out_idx];
   const bool ok = tracked(r);
+  if (ok && blockIdx.x == 0 && tid == 0) atomicAdd(cnt, 1u);
   for (int k = tid; k < H; k += kRefThreads) px[k] = ok ? shift_phase(k, N, r.d[1]) : make_float2(0.f, 0.f);
   for (int k = tid; k < kAlignRows; k += kRefThreads)
     py[k] = (ok && y0 + k < N) ? shift_phase(y0 + k, N, r.d[0]) : make_float2(0.f, 0.f);
@@ -61,21 +63,72 @@ __global__ void __launch_bounds__(kRefThreads) k_align_spectra(const FrameDesc* 
   }
 }
 
-// acc[k] += sum over the chunk's frames of F[f][k], frames in order.
+// The same from the frame itself, for frames that fit LDS: one block per frame
+// transforms it there and writes the aligned spectrum, where the passes write
+// and read two spectra more (256 frames of 192 x 192: 58 us -> 33).  The bits
+// are those of the passes; launches split between the two as the correlation
+// does (whole mean at 192 x 192, passes / LDS: 64 frames 46 / 47 us, 128 frames
+// 60 / 54; at 128 x 128 one frame takes 28 / 28).
 template <int N>
-__global__ void k_sum_spectra(int count, const float2* __restrict__ F, float2* __restrict__ acc) {
-  constexpr int H = N / 2 + 1;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= N * H) return;
-  float2 sum = make_float2(0.f, 0.f);
-  for (int f = 0; f < count; ++f) sum = cadd(sum, F[(size_t)f * N * H + e]);
-  acc[e] = cadd(acc[e], sum);
+__global__ void __launch_bounds__(lds::lds_threads(N, N)) k_align_lds(const FrameDesc* __restrict__ desc, int first,
+                                                                      const ccpt_result* __restrict__ fwd,
+                                                                      const float2* __restrict__ gtw,
+                                                                      float2* __restrict__ F,
+                                                                      unsigned* __restrict__ cnt) {
+  using namespace lds;
+  constexpr int THR = lds_threads(N, N), H = N / 2 + 1, S = Col<N>::S;
+  __shared__ float2 m[H * S];
+  __shared__ float2 tw[N];
+  __shared__ float2 px[H], py[N];
+  const int f = blockIdx.x;
+  const FrameDesc d = desc[first + f];
+  const ccpt_result& r = fwd[d.out_idx];
+  float2* Ff = F + (size_t)f * N * H;
+  if (!tracked(r)) {  // (it may hold NaN: zeros, not a scaled spectrum)
+    for (unsigned i = threadIdx.x; i < N * H; i += THR) Ff[i] = make_float2(0.f, 0.f);
+    return;
+  }
+  if (threadIdx.x == 0) atomicAdd(cnt, 1u);
+  for (int i = threadIdx.x; i < N; i += THR) tw[i] = gtw[i];
+  unsigned kmin, kmax, bad;
+  load_frame<N, N, THR>(d, false, 0.f, false, m, kmin, kmax, bad);
+  for (int k = threadIdx.x; k < N + H; k += THR) {
+    if (k < N)
+      py[k] = shift_phase(k, N, r.d[0]);
+    else
+      px[k - N] = shift_phase(k - N, N, r.d[1]);
+  }
+  __syncthreads();
+  rows_forward<N, N, THR>(m, tw, gtw);
+  stages<N, -1, H, N, N, false, THR, false, 0, 1>(m, tw, gtw, NoUse());
+  for (unsigned i = fresh_tid(); i < N * H; i += THR) {
+    const unsigned y = i / H, kx = i % H;
+    Ff[i] = cmul(m[at<N, false>(kx, y)], cmul(py[y], px[kx]));
+  }
 }
 
-__global__ void k_count_tracked(const FrameDesc* __restrict__ desc, int first, int count,
-                                const ccpt_result* __restrict__ fwd, unsigned* __restrict__ cnt) {
-  const int f = blockIdx.x * blockDim.x + threadIdx.x;
-  if (f < count && tracked(fwd[desc[first + f].out_idx])) atomicAdd(cnt, 1u);
+// acc[k] += sum over the chunk's frames of F[f][k], frames in order: one chain
+// of additions per element, so it is the loads that have to overlap.  kSumLoads
+// of them are in flight per thread (256 frames of 192 x 192: 64 us with one,
+// 13 with them), and small blocks spread a frame's elements over the CUs.
+constexpr int kSumThreads = 64, kSumLoads = 32;
+
+template <int N>
+__global__ void __launch_bounds__(kSumThreads) k_sum_spectra(int count, const float2* __restrict__ F,
+                                                             float2* __restrict__ acc) {
+  constexpr int NH = N * (N / 2 + 1);
+  const int e = blockIdx.x * kSumThreads + threadIdx.x;
+  if (e >= NH) return;
+  float2 sum = make_float2(0.f, 0.f);
+  for (int f0 = 0; f0 < count; f0 += kSumLoads) {
+    float2 v[kSumLoads];
+#pragma unroll
+    for (int j = 0; j < kSumLoads; ++j) v[j] = F[(size_t)min(f0 + j, count - 1) * NH + e];
+#pragma unroll
+    for (int j = 0; j < kSumLoads; ++j)
+      if (f0 + j < count) sum = cadd(sum, v[j]);
+  }
+  acc[e] = cadd(acc[e], sum);
 }
 
 // img *= scale / count (count >= 1; an empty mean is left as zeros)
@@ -131,25 +184,44 @@ static int rt_update_n(const ccpt_result* res, const float2* F, float2* S, float
 }
 
 template <int N>
-static int align_accumulate_n(const FrameDesc* desc, int first, int count, const ccpt_result* fwd,
-                              float2* F, float2* acc, unsigned* cnt, hipStream_t s) {
-  constexpr int H = N / 2 + 1;
-  hipLaunchKernelGGL((k_align_spectra<N>), dim3((N + kAlignRows - 1) / kAlignRows, count),
-                     dim3(kRefThreads), 0, s, desc, first, fwd, F);
-  hipLaunchKernelGGL((k_sum_spectra<N>), dim3((N * H + 255) / 256), dim3(256), 0, s, count,
-                     (const float2*)F, acc);
-  hipLaunchKernelGGL(k_count_tracked, dim3((count + 255) / 256), dim3(256), 0, s, desc, first,
-                     count, fwd, cnt);
+static int align_n(const FrameDesc* desc, int first, int count, const ccpt_result* fwd, float2* F, unsigned* cnt,
+                   hipStream_t s) {
+  hipLaunchKernelGGL((k_align_spectra<N>), dim3((N + kAlignRows - 1) / kAlignRows, count), dim3(kRefThreads), 0, s,
+                     desc, first, fwd, F, cnt);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-int launch_align_accumulate(int N, const FrameDesc* desc, int first, int count,
-                            const ccpt_result* fwd, float2* F, float2* acc, unsigned* cnt,
-                            hipStream_t s) {
+int launch_align(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd, float2* F, unsigned* cnt,
+                 hipStream_t s) {
   switch (N) {
 #define CASE(n) \
   case n:       \
-    return align_accumulate_n<n>(desc, first, count, fwd, F, acc, cnt, s);
+    return align_n<n>(desc, first, count, fwd, F, cnt, s);
+    CCPT_FOR_SIZES(CASE)
+#undef CASE
+  }
+  return -2;
+}
+
+int launch_align_lds(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd, const float2* tw,
+                     float2* F, unsigned* cnt, hipStream_t s) {
+#define CASE(n, n2)                                                                                              \
+  if (N == n) {                                                                                                  \
+    hipLaunchKernelGGL((k_align_lds<n>), dim3(count), dim3(lds::lds_threads(n, n)), 0, s, desc, first, fwd, tw, F, cnt); \
+    return hipGetLastError() == hipSuccess ? 0 : -1;                                                             \
+  }
+  CCPT_FOR_LDS_SQUARE(CASE)
+#undef CASE
+  return -2;
+}
+
+int launch_sum_spectra(int N, int count, const float2* F, float2* acc, hipStream_t s) {
+  switch (N) {
+#define CASE(n)                                                                                                \
+  case n:                                                                                                      \
+    hipLaunchKernelGGL((k_sum_spectra<n>), dim3((n * (n / 2 + 1) + kSumThreads - 1) / kSumThreads), dim3(kSumThreads), \
+                       0, s, count, F, acc);                                                                   \
+    return hipGetLastError() == hipSuccess ? 0 : -1;
     CCPT_FOR_SIZES(CASE)
 #undef CASE
   }

@@ -361,7 +361,7 @@ def main():
                          "the committed rocprofv3 summary); 0: the autotuner's choice")
     ap.add_argument("--streams", type=int, default=2, choices=[1, 2],
                     help="streams of the timed headline leg: 2 runs alternate launch chunks on two streams "
-                         "(CCPT_FLAG_STREAMS: one chunk's DFT overlaps the next chunk's correlation; results "
+                         "(CCPT_FLAG_STREAMS: one chunk's window expansion overlaps the next chunk's correlation; results "
                          "bit-identical to one stream); the per-kernel roofline always comes from a one-stream "
                          "pass with HIP events around each launch")
     ap.add_argument("--copy-calib-mib", type=int, default=0,

@@ -312,8 +312,11 @@ int ccpt_drift_filter(const double* r, int n, double a0, double rate_limit, doub
                       double* out);
 
 /* Launch scheduling of the batched path (a10): frames of one size are run in
-   chunks whose spectra workspace stays resident in the Infinity Cache; the
-   chunk size trades that residency against the number of launches.
+   chunks; the chunk size trades the spectra's residency in the Infinity Cache
+   against the number of launches and their uneven last rounds of blocks.  The
+   default is 768 frames (more for small ones; at most 2 GB of workspace, 192 MB
+   where the card has no room for that), and a chunk may take a quarter more
+   rather than leave a small one for the end.
    ccpt_autotune times ccpt_track_batch on `batch` frames of size n x n (each
    frame is the context's reference of that size; timing does not depend on
    content) over chunk sizes and the block plans of ccpt_plan, and keeps the
@@ -336,7 +339,9 @@ typedef struct ccpt_plan {
                        (latency); -1 = default (128), 0 = never; at most 512 */
   int fused_min;    /* 256 x 256 frames: launches of at least this many frames take
                        the one-kernel correlation stage (one frame per CU), smaller
-                       ones the three passes; -1 = default (128) */
+                       ones the three passes; -1 = default (128).  With the
+                       default chunk this goes by units of the frames whose
+                       spectra fill 192 MB (381 in FP32), whatever the launches */
 } ccpt_plan;
 
 /* Reads the plan in force for ny x nx frames (defaults filled in), or sets

@@ -297,12 +297,11 @@ size_t frame_ws_bytes(int n, int precision) {
   return t_bytes(n, precision) + spec_elems(n) * sizeof(float2);
 }
 
-// Default frames per chunk: 192 MB of spectra, well inside the 256 MB
-// Infinity Cache.  The split precisions count a second copy of the spectrum,
-// which they no longer keep: 256 x 256 groups take the one-kernel correlation
-// or the three passes by the size of their chunks, and a chunk of another
-// size would change which frames' sums run in which order.
-int default_chunk(int n, int precision) {
+// Frames whose spectra fill 192 MB.  (The split precisions count a second copy
+// of the spectrum, which they no longer keep.)  256 x 256 groups take the
+// one-kernel correlation or the three passes by units of this size (launches()),
+// and a unit of another size would change which frames' sums run in which order.
+int unit_frames(int n, int precision) {
   const size_t budget = (size_t)192 << 20;
   size_t b = 2 * spec_elems(n) * (precision == CCPT_PREC_FP64 ? sizeof(double2) : sizeof(float2));
   if (precision == CCPT_PREC_FP64)
@@ -314,10 +313,26 @@ int default_chunk(int n, int precision) {
   return std::max(1, std::min(c, 4096));
 }
 
-int chunk_for(const ccpt_ctx* ctx, int n) {
+// Default frames per launch: three blocks per CU of the kernels that take a
+// frame per block, or 192 MB of spectra where that is more (and at most 2 GB).
+// Small launches cost more than spectra that outgrow the Infinity Cache: us per
+// call, launches that stay inside it -> of up to 768 frames, 2048 frames of 256 x 256
+// 907 -> 673 (381 frames are a round and a half of blocks; 512, 1024 and 2048
+// a launch take 675, 723 and 694), 512 of 512 x 512 1402 -> 1094 (64, 128 and
+// 256 a launch: 1372, 1345, 1193), 512 of 128 x 256 184 -> 141.
+int default_chunk(int n, int precision) {
+  const size_t cap = ((size_t)2 << 30) / frame_ws_bytes(n, precision);
+  return std::max(unit_frames(n, precision), (int)std::min<size_t>(768, cap));
+}
+
+int set_chunk(const ccpt_ctx* ctx, int n) {
   auto it = ctx->sched.find(n);
-  if (it != ctx->sched.end() && it->second.chunk > 0) return it->second.chunk;
-  return default_chunk(n, ctx->o.precision);
+  return it != ctx->sched.end() && it->second.chunk > 0 ? it->second.chunk : 0;
+}
+
+int chunk_for(const ccpt_ctx* ctx, int n) {
+  const int c = set_chunk(ctx, n);
+  return c > 0 ? c : default_chunk(n, ctx->o.precision);
 }
 
 int split_blocks_for(const ccpt_ctx* ctx, int n) {
@@ -345,6 +360,52 @@ int fused_min_for(const ccpt_ctx* ctx, int n) {
   return kFusedMinFrames;
 }
 
+// One launch of a group: its frames and the 256 x 256 correlation's threshold.
+struct Launch {
+  int count, fused_min;
+};
+
+// The launches of a group of `count` frames of shape code n.  A chunk size that
+// the plan sets is taken as it is; so are `limit` frames (> 0: the static
+// scratch, or `small`: what fits 192 MB).  Default launches may take a quarter
+// more than default_chunk instead of leaving a small one for the end.  Frames of
+// 256 x 256 take the correlation that they take in units of unit_frames: the
+// one-kernel one, but for a last unit below fused_min.
+std::vector<Launch> launches(const ccpt_ctx* ctx, int n, int count, bool small, int limit) {
+  std::vector<Launch> v;
+  const int fm = fused_min_for(ctx, n);
+  const int set = set_chunk(ctx, n);
+  const int unit = set > 0 ? set : unit_frames(n, ctx->o.precision);
+  if (set > 0 || small || limit > 0) {
+    const int c = limit > 0 ? std::min(unit, limit) : unit;
+    for (int left = count; left > 0 && c > 0; left -= c) v.push_back(Launch{std::min(c, left), fm});
+    return v;
+  }
+  const int chunk = default_chunk(n, ctx->o.precision);
+  auto split = [&](int left, int f) {
+    while (left > 0) {
+      const int c = left <= chunk + chunk / 4 ? left : chunk;
+      v.push_back(Launch{c, f});
+      left -= c;
+    }
+  };
+  if (code_ny(n) != 256 || code_nx(n) != 256) {
+    split(count, fm);
+    return v;
+  }
+  int fused = 0;  // frames of the units that reach fused_min
+  if (std::min(unit, count) >= fm) fused = count % unit >= fm ? count : count - count % unit;
+  split(fused, 1);
+  split(count - fused, 1 << 30);
+  return v;
+}
+
+int largest(const std::vector<Launch>& v) {
+  int m = 0;
+  for (const Launch& l : v) m = std::max(m, l.count);
+  return m;
+}
+
 // Device memory the launches of one call work in: the context's buffers
 // (ccpt_track_batch) or the library's static scratch (ccpt_track_batch_static).
 struct CallMem {
@@ -353,6 +414,7 @@ struct CallMem {
   FrameState* st = nullptr;    // frame states, slot_st entries per slot
   size_t slot_st = 0;
   size_t chunk_bytes = 0;      // > 0: chunks limited to this much workspace
+  bool small = false;          // launches of what fits 192 MB
   bool slots = true;           // two chunk slots allowed (CCPT_FLAG_STREAMS)
   bool mark = true;            // profiling events allowed
   bool* st_dirty = nullptr;    // set while a chunk's states may be left non-initial
@@ -495,19 +557,20 @@ bool pairs_ok(const std::vector<FrameDesc>& desc, int first, int count) {
 
 int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc, int first,
               int count, ccpt_result* out, hipStream_t s, bool pairs) {
-  int chunk = std::min(count, chunk_for(ctx, n));
+  int limit = 0;
   if (mem.chunk_bytes) {
-    chunk = std::min<int>(chunk, (int)(mem.chunk_bytes / frame_ws_bytes(n, ctx->o.precision)));
-    chunk = std::min<int>(chunk, (int)mem.slot_st);
+    limit = std::min<int>((int)(mem.chunk_bytes / frame_ws_bytes(n, ctx->o.precision)), (int)mem.slot_st);
+    if (limit < 1) return fail(ctx, CCPT_E_INVALID, "no workspace for one frame");
   }
-  if (chunk < 1) return fail(ctx, CCPT_E_INVALID, "no workspace for one frame");
+  const std::vector<Launch> ls = launches(ctx, n, count, mem.small, limit);
+  const int chunk = largest(ls);
   SizeTables& t = ctx->tables[table_key(n)];
   const int ny = code_ny(n), nx = code_nx(n);
   const WindowTables wt{t.gy, t.gx, t.gxn, ctx->tf, ctx->td, t.ksteps, ctx->half};
   const Marker mark = mem.mark ? marker_of(ctx, s) : Marker{};
   // several chunks: alternate between the two slots (streams s and aux),
   // forked from and joined back into s
-  const bool two = count > chunk && mem.slots && use_slots(ctx);
+  const bool two = ls.size() > 1 && mem.slots && use_slots(ctx);
   if (two) {
     HIP_CHECK(ctx, hipEventRecord(ctx->fork_evt, s));
     HIP_CHECK(ctx, hipStreamWaitEvent(ctx->aux, ctx->fork_evt, 0));
@@ -517,14 +580,16 @@ int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc,
     if (two) (void)hipStreamSynchronize(ctx->aux);
     return fail(ctx, CCPT_E_HIP, "%s launch failed", what);
   };
-  for (int c0 = 0, ci = 0; c0 < count; c0 += chunk, ++ci) {
-    const int slot = two ? (ci & 1) : 0;
+  int c0 = 0;
+  for (size_t ci = 0; ci < ls.size(); c0 += ls[ci++].count) {
+    const int slot = two ? (int)(ci & 1) : 0;
     hipStream_t cs = slot ? ctx->aux : s;
     GroupParams g = base_params(ctx, n);
     g.pairs_ok = pairs ? 1 : 0;
     g.desc = d_desc;
     g.first = first + c0;
-    g.count = std::min(chunk, count - c0);
+    g.count = ls[ci].count;
+    g.fused_min = ls[ci].fused_min;
     g.out = out;
     carve(ctx, mem, n, chunk, slot, g);
     const int parts = window_parts(ctx, n, g.count);
@@ -948,22 +1013,38 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   }
   // per-lane needs (one lane: per chunk slot, two slots when some group has
   // several chunks and two-stream chunks are on)
-  std::vector<size_t> lws(nl, 0), lst(nl, 0);
+  std::vector<size_t> lws, lst, ows, ost;
   int nslots = 1;
-  for (int gi = 0; gi < ngroups; ++gi) {
-    const int nn = sig[2 * gi], cnt = sig[2 * gi + 1], l = lane_of[gi];
-    const int chunk = std::min(cnt, chunk_for(ctx, nn));
-    lws[l] = std::max(lws[l], frame_ws_bytes(nn, ctx->o.precision) * (size_t)chunk + 256);
-    lst[l] = std::max(lst[l], (size_t)chunk);
-    if (nl == 1 && cnt > chunk && use_slots(ctx)) nslots = 2;
-  }
-  std::vector<size_t> ows(nl + 1, 0), ost(nl + 1, 0);
-  for (int l = 0; l < nl; ++l) {
-    lws[l] = (lws[l] + 255) / 256 * 256;
-    ows[l + 1] = ows[l] + lws[l] * nslots;
-    ost[l + 1] = ost[l] + lst[l] * nslots;
-  }
+  auto layout = [&](bool small) {
+    lws.assign(nl, 0);
+    lst.assign(nl, 0);
+    nslots = 1;
+    for (int gi = 0; gi < ngroups; ++gi) {
+      const int nn = sig[2 * gi], cnt = sig[2 * gi + 1], l = lane_of[gi];
+      const std::vector<Launch> ls = launches(ctx, nn, cnt, small, 0);
+      const int chunk = largest(ls);
+      lws[l] = std::max(lws[l], frame_ws_bytes(nn, ctx->o.precision) * (size_t)chunk + 256);
+      lst[l] = std::max(lst[l], (size_t)chunk);
+      if (nl == 1 && ls.size() > 1 && use_slots(ctx)) nslots = 2;
+    }
+    ows.assign(nl + 1, 0);
+    ost.assign(nl + 1, 0);
+    for (int l = 0; l < nl; ++l) {
+      lws[l] = (lws[l] + 255) / 256 * 256;
+      ows[l + 1] = ows[l] + lws[l] * nslots;
+      ost[l + 1] = ost[l] + lst[l] * nslots;
+    }
+  };
+  // a card with no room for the launches' workspace takes smaller ones
+  bool small = false;
+  layout(small);
   rc = ensure_ws(ctx, ows[nl]);
+  if (rc == CCPT_E_NOMEM) {
+    (void)hipGetLastError();  // the refused allocation is not a launch's error
+    small = true;
+    layout(small);
+    rc = ensure_ws(ctx, ows[nl]);
+  }
   if (rc) return rc;
   ctx->slot_ws = lws[0];
   rc = ensure_state(ctx, ost[nl], s);
@@ -988,6 +1069,7 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
       mem.st = ctx->st_buf + ost[l];
       mem.slot_st = lst[l];
       if (nl > 1) mem.slots = false;
+      mem.small = small;
       hipStream_t ls = l ? ctx->lane_s[l - 1] : s;
       for (int gi = 0; gi < ngroups && r2 == CCPT_OK; ++gi) {
         if (lane_of[gi] != l) continue;

@@ -1316,10 +1316,10 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
         g.first = f0 + nl;
         g.count = count - nl;
         if (g_ref) g.QB = QB + spec * nl;
-        if ((g_ref && launch_frame_spectra(nn, nn, 0, ctx->d_desc, g.first, g.count, mode, eps, T, FA, tw, s)) ||
+        if ((g_ref && launch_frame_spectra(nn, ctx->d_desc, g.first, g.count, mode, eps, T, FA, tw, s)) ||
             launch_grad_psi(nn, g, FA, QA, s))
           return fail(ctx, CCPT_E_HIP, "gradient launch failed");
-        if (g_frames && (launch_inverse(nn, nn, QA, g.count, 2.0f, T, img, tw, s) ||
+        if (g_frames && (launch_inverse(nn, QA, g.count, 2.0f, T, img, tw, s) ||
                          launch_grad_frames(nn, ctx->d_desc, g.first, g.count, img, d_goff, g_frames, mode,
                                             eps, s)))
           return fail(ctx, CCPT_E_HIP, "frame gradient launch failed");
@@ -1339,7 +1339,7 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
       const int nn = ctx->refs[r].n;
       float2* T = (float2*)ctx->ws;
       float* img = (float*)(T + spec_elems(nn));
-      if (launch_inverse(nn, nn, (float2*)ctx->acc_buf + aoff[r], 1, 2.0f, T, img, ctx->tables[nn].tw,
+      if (launch_inverse(nn, (float2*)ctx->acc_buf + aoff[r], 1, 2.0f, T, img, ctx->tables[nn].tw,
                          s) ||
           launch_grad_ref_chain(img, ctx->refs[r].img, nn * nn, mode, eps, g_ref + roff[r], s))
         return fail(ctx, CCPT_E_HIP, "reference gradient launch failed");
@@ -1388,8 +1388,8 @@ int ccpt_fisher(ccpt_ctx* ctx, const ccpt_image* mu, double* fisher, void* strea
   const float2* tw = ctx->tables[n].tw;
   int bad = launch_spectrum(n, n, mu->data, mu->dtype, mu->pitch, 0, 0, 1, 0, 0.f, 0, T, F, tw,
                             s) ||
-            launch_fisher_deriv(n, F, Dy, Dx, s) || launch_inverse(n, n, Dy, 1, 2.0f, T, iy, tw, s) ||
-            launch_inverse(n, n, Dx, 1, 2.0f, T, ix, tw, s) ||
+            launch_fisher_deriv(n, F, Dy, Dx, s) || launch_inverse(n, Dy, 1, 2.0f, T, iy, tw, s) ||
+            launch_inverse(n, Dx, 1, 2.0f, T, ix, tw, s) ||
             launch_fisher_reduce(iy, ix, mu->data, mu->dtype, mu->pitch, n, part, nblocks, fisher, s);
   hipError_t e = hipStreamSynchronize(s);
   (void)hipFree(tmp);
@@ -1438,13 +1438,13 @@ int ccpt_mean_aligned(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_res
     float2* Fr = F + spec * nl;
     if ((nl > 0 && launch_align_lds(N, ctx->d_desc, c0, nl, fwd, tw, F, cnt, s)) ||
         (rest > 0 &&
-         (launch_frame_spectra(N, N, 0, ctx->d_desc, c0 + nl, rest, CCPT_MODE_CCU, 0.f, T, Fr, tw, s) ||
+         (launch_frame_spectra(N, ctx->d_desc, c0 + nl, rest, CCPT_MODE_CCU, 0.f, T, Fr, tw, s) ||
           launch_align(N, ctx->d_desc, c0 + nl, rest, fwd, Fr, cnt, s))) ||
         launch_sum_spectra(N, count, F, acc, s))
       return fail(ctx, CCPT_E_HIP, "alignment launch failed");
   }
   // the row pass of the inverse returns half the unnormalised transform
-  if (launch_inverse(N, N, acc, 1, 2.0f / ((float)N * (float)N), T, out, tw, s) ||
+  if (launch_inverse(N, acc, 1, 2.0f / ((float)N * (float)N), T, out, tw, s) ||
       launch_scale_by_count(out, N * N, 1.0f, cnt, s))
     return fail(ctx, CCPT_E_HIP, "inverse launch failed");
   return CCPT_OK;
@@ -1463,31 +1463,16 @@ int ccpt_track_update(ccpt_ctx* ctx, const ccpt_roi* roi, double a0, ccpt_result
   const int code = R.n;
   const int ny = code_ny(code), nx = code_nx(code), tr = code_trans(code);
   const size_t spec = spec_elems(code);
-  // scratch: two spectra, and for a rectangle in CC-SN the updated E in the
-  // tall layout (the context's copy of a rectangle's E is read by nothing:
-  // the adjoint takes square frames only)
-  const size_t img_bytes = is_rect(code) ? (size_t)ny * nx * sizeof(float) : 0;
-  rc = ensure_buf(ctx, ctx->rt_buf, ctx->rt_cap, 2 * spec * sizeof(float2) + img_bytes);
+  // (the context's copy of a rectangle's E is read by nothing: the adjoint
+  // takes square frames only)
+  rc = ensure_buf(ctx, ctx->rt_buf, ctx->rt_cap, spec * sizeof(float2));
   if (rc) return rc;
-  float2* T = (float2*)ctx->rt_buf;
-  float2* F = T + spec;
-  float* img = is_rect(code) ? (float*)(F + spec) : R.img;
-  const float2* tw = ctx->tables[table_key(code)].tw;
-  const float fa0 = (float)a0, fb1 = (float)(1.0 - a0);
-  // the frame's own spectrum F[I] (track_batch left its descriptor at index 0)
-  if (launch_frame_spectra(ny, nx, tr, ctx->d_desc, 0, 1, CCPT_MODE_CCU, 0.f, T, F, tw, s))
-    return fail(ctx, CCPT_E_HIP, "frame spectrum launch failed");
-  if (ctx->o.mode == CCPT_MODE_CCU) {
-    if (launch_rt_update(ny, nx, tr, out, F, R.spec, fa0, fb1, 1, s))
-      return fail(ctx, CCPT_E_HIP, "reference update launch failed");
-  } else {
-    // update F[E], then E (tall layout), then conj F[-1/(E+eps)]
-    if (launch_rt_update(ny, nx, tr, out, F, R.espec, fa0, fb1, 0, s) ||
-        launch_inverse(ny, nx, R.espec, 1, 2.0f / ((float)ny * (float)nx), T, img, tw, s) ||
-        launch_spectrum(ny, nx, img, CCPT_F32, nx, 0, 0, 1, 1, (float)ctx->o.eps, 1, T, R.spec, tw,
-                        s))
-      return fail(ctx, CCPT_E_HIP, "reference update launch failed");
-  }
+  const bool sn = ctx->o.mode == CCPT_MODE_CCSN;
+  // (track_batch left the frame's descriptor at index 0)
+  const RtUpdate u{ctx->d_desc, out, (float2*)ctx->rt_buf, R.spec, sn ? R.espec : nullptr,
+                   is_rect(code) ? nullptr : R.img, (float)a0, (float)(1.0 - a0), (float)ctx->o.eps,
+                   ctx->tables[table_key(code)].tw};
+  if (launch_rt_update(ny, nx, tr, u, s)) return fail(ctx, CCPT_E_HIP, "reference update launch failed");
   return CCPT_OK;
 }
 

@@ -274,18 +274,15 @@ int launch_window_coef(int ny, int nx, const GroupParams& g, const WindowTables&
 int launch_window_max(int ny, int nx, const GroupParams& g, const WindowTables& t, int nparts,
                       double step_limit, hipStream_t s);
 
-// Inverse 2-D c2r of n half spectra [n][ny][nx/2+1] into n float images of
-// ny rows of nx (the tall layout of a rectangle) scaled by `scale` (T is
-// scratch of the same size as the spectra).
-int launch_inverse(int ny, int nx, const float2* spec, int n, float scale, float2* T, float* img,
-                   const float2* tw, hipStream_t s);
+// Inverse 2-D c2r of n half spectra [n][N][N/2+1] into n float images scaled by
+// `scale` (T is scratch of the same size as the spectra).
+int launch_inverse(int N, const float2* spec, int n, float scale, float2* T, float* img, const float2* tw,
+                   hipStream_t s);
 
-// Forward 2-D r2c spectra (with the frame prologue of `mode`) of the frames of
-// a descriptor chunk into spec [count][ny][nx/2+1], held tall (trans: wide
-// frames read transposed).
-int launch_frame_spectra(int ny, int nx, int trans, const FrameDesc* desc, int first, int count,
-                         int mode, float eps, float2* T, float2* spec, const float2* tw,
-                         hipStream_t s);
+// Forward 2-D r2c spectra (with the frame prologue of `mode`) of the square
+// frames of a descriptor chunk into spec [count][N][N/2+1].
+int launch_frame_spectra(int N, const FrameDesc* desc, int first, int count, int mode, float eps, float2* T,
+                         float2* spec, const float2* tw, hipStream_t s);
 
 // Adjoint (grad.hip).  Parameters of a launch over frames [first, first + count)
 // of the descriptors; QB (or null) and the products are indexed from `first`.
@@ -335,12 +332,22 @@ int launch_align(int N, const FrameDesc* desc, int first, int count, const ccpt_
 int launch_align_lds(int N, const FrameDesc* desc, int first, int count, const ccpt_result* fwd, const float2* tw,
                      float2* F, unsigned* cnt, hipStream_t s);
 int launch_sum_spectra(int N, int count, const float2* F, float2* acc, hipStream_t s);
-// Real-time reference update of Eq. 9 by one frame (spectrum F, result res):
-// S <- a0 v + b1 S with v the frame shifted back (conjugated when conj_s);
-// spectra held tall, ny x (nx/2+1) (trans: a wide frame, whose shift axes
-// swap in that layout).
-int launch_rt_update(int ny, int nx, int trans, const ccpt_result* res, const float2* F, float2* S,
-                     float a0, float b1, int conj_s, hipStream_t s);
+// Real-time reference update of Eq. 9 (xcorr.hip) by the frame of descriptor 0
+// and its result: S <- a0 v + b1 S with v the frame shifted back; S = rspec =
+// conj F[E] in CC-U, S = espec = F[E] in CC-SN, where E (to img unless null) and
+// rspec = conj F[-1/(E+eps)] follow from it.  Spectra held tall, ny x (nx/2+1)
+// (trans: a wide frame, whose shift axes swap in that layout); T is scratch.
+struct RtUpdate {
+  const FrameDesc* desc;
+  const ccpt_result* res;
+  float2* T;
+  float2* rspec;
+  float2* espec;  // null: CC-U
+  float* img;
+  float a0, b1, eps;
+  const float2* tw;
+};
+int launch_rt_update(int ny, int nx, int trans, const RtUpdate& u, hipStream_t s);
 // References: sets *flag (zeroed before) if a pixel is not finite or, in CC-SN,
 // E + eps <= 0; the float copy [ny][nx] of an image.
 int launch_ref_check(const void* data, int dtype, int pitch, int ny, int nx, int mode, double eps,

@@ -15,24 +15,12 @@
 
 #include "common.h"
 #include "lds_frame.h"
+#include "shift.h"
 
 namespace ccpt {
 
 constexpr int kRefThreads = 256;
 constexpr int kAlignRows = 8;  // spectrum rows per block of k_align_spectra
-
-__device__ __forceinline__ bool tracked(const ccpt_result& r) {
-  return !(r.status & (CCPT_ST_NONFINITE | CCPT_ST_FLAT));
-}
-
-// phi_k(d) of one axis as FP32 complex, computed in FP64.
-__device__ __forceinline__ float2 shift_phase(int k, int N, double d) {
-  if (2 * k == N) return make_float2((float)cospi(d), 0.f);
-  const int kt = 2 * k < N ? k : k - N;
-  double sn, cs;
-  sincospi(2.0 * (double)kt * d / (double)N, &sn, &cs);
-  return make_float2((float)cs, (float)sn);
-}
 
 // F[f] (row-major N x (N/2+1)) *= phi_ky(d_y) phi_kx(d_x) for frame f's
 // displacement; frames that did not track are zeroed, the others counted.
@@ -140,49 +128,6 @@ __global__ void k_scale_by_count(float* __restrict__ img, int nn, float scale,
     img[i] *= s;
 }
 
-// Real-time reference update (Sec. III.B, Eq. 9) by one frame with spectrum
-// F (row-major NY x (NX/2+1), the tall layout) and result res: v = F
-// phi_ky(d_y) phi_kx(d_x) (the frame shifted back; for a wide frame, held
-// transposed, the spectrum's rows run along the frame's x) enters the
-// resident spectrum S as
-//   S <- a0 conj(v) + b1 S   (conj_s: S = conj F[E], the CC-U reference)
-//   S <- a0 v + b1 S         (S = F[E], kept for CC-SN)
-// and a frame that did not track leaves S unchanged.
-template <int NY, int NX>
-__global__ void __launch_bounds__(kRefThreads) k_rt_update(const ccpt_result* __restrict__ res,
-                                                           const float2* __restrict__ F,
-                                                           float2* __restrict__ S, float a0,
-                                                           float b1, int conj_s, int trans) {
-  constexpr int H = NX / 2 + 1;
-  __shared__ float2 px[H];
-  __shared__ float2 py[kAlignRows];
-  const int y0 = blockIdx.x * kAlignRows, tid = threadIdx.x;
-  const ccpt_result r = *res;
-  if (!tracked(r)) return;
-  const double dy = trans ? r.d[1] : r.d[0], dx = trans ? r.d[0] : r.d[1];
-  for (int k = tid; k < H; k += kRefThreads) px[k] = shift_phase(k, NX, dx);
-  for (int k = tid; k < kAlignRows; k += kRefThreads)
-    py[k] = y0 + k < NY ? shift_phase(y0 + k, NY, dy) : make_float2(0.f, 0.f);
-  __syncthreads();
-  const int rows = min(kAlignRows, NY - y0);
-  for (int i = tid; i < rows * H; i += kRefThreads) {
-    const int ry = i / H, kx = i - ry * H;
-    const size_t e = (size_t)(y0 + ry) * H + kx;
-    float2 v = cmul(F[e], cmul(py[ry], px[kx]));
-    if (conj_s) v = cconj(v);
-    const float2 o = S[e];
-    S[e] = make_float2(a0 * v.x + b1 * o.x, a0 * v.y + b1 * o.y);
-  }
-}
-
-template <int NY, int NX>
-static int rt_update_n(const ccpt_result* res, const float2* F, float2* S, float a0, float b1,
-                       int conj_s, int trans, hipStream_t s) {
-  hipLaunchKernelGGL((k_rt_update<NY, NX>), dim3((NY + kAlignRows - 1) / kAlignRows),
-                     dim3(kRefThreads), 0, s, res, F, S, a0, b1, conj_s, trans);
-  return hipGetLastError() == hipSuccess ? 0 : -1;
-}
-
 template <int N>
 static int align_n(const FrameDesc* desc, int first, int count, const ccpt_result* fwd, float2* F, unsigned* cnt,
                    hipStream_t s) {
@@ -225,25 +170,6 @@ int launch_sum_spectra(int N, int count, const float2* F, float2* acc, hipStream
     CCPT_FOR_SIZES(CASE)
 #undef CASE
   }
-  return -2;
-}
-
-int launch_rt_update(int ny, int nx, int trans, const ccpt_result* res, const float2* F, float2* S,
-                     float a0, float b1, int conj_s, hipStream_t s) {
-  if (ny == nx) {
-    switch (ny) {
-#define CASE(n) \
-  case n:       \
-    return rt_update_n<n, n>(res, F, S, a0, b1, conj_s, 0, s);
-      CCPT_FOR_SIZES(CASE)
-#undef CASE
-    }
-    return -2;
-  }
-#define CASE(a, b) \
-  if (ny == a && nx == b) return rt_update_n<a, b>(res, F, S, a0, b1, conj_s, trans, s);
-  CCPT_FOR_RECT(CASE)
-#undef CASE
   return -2;
 }
 

@@ -11,6 +11,7 @@
 
 #include "common.h"
 #include "fft.h"
+#include "shift.h"
 
 namespace ccpt {
 
@@ -117,6 +118,76 @@ __global__ void k_init_state(FrameState* st, int count) {
   }
 }
 
+// Transformed rows y0 .. y0 + RPB - 1 to bins: X[k] = E[k] + W^k O[k],
+// E = (Z[k] + conj Z[L-k]) / 2, O = (Z[k] - conj Z[L-k]) / (2i),
+// W = exp(-2 pi i / NX); stored column-major Tf[k][y] so each column k receives
+// RPB consecutive rows.
+template <int NY, int NX, int RPB, typename C>
+__device__ __forceinline__ void unpack_rows(const C* z, const C* tw, C* __restrict__ Tf, int y0) {
+  using R = real_t<C>;
+  constexpr int L = NX / 2, H = NX / 2 + 1, LS = lds_len(L) + 1;
+  const R half = R(0.5);
+  for (unsigned i = threadIdx.x; i < (unsigned)(RPB * H); i += kThreads) {
+    const unsigned k = i / RPB, r = i % RPB;
+    const C zk = z[r * LS + lds_idx(k == L ? 0 : k)];
+    const C zc = cconj(z[r * LS + lds_idx(k == 0 ? 0 : L - k)]);
+    const C e = cscale(cadd(zk, zc), half);
+    const C d = csub(zk, zc);
+    const C o = mkc<C>(half * d.y, -half * d.x);  // d / (2i)
+    Tf[(size_t)k * NY + y0 + r] = cadd(e, cmul(tw[k], o));
+  }
+}
+
+// Rows y0 .. y0 + RPB - 1 of column-major bins to transformed rows in LDS: the
+// NX/2+1 bins of a row packed into NX/2 complex values Z = E + i O with
+// E = (X[k] + conj X[L-k]) / 2 and O = (X[k] - conj X[L-k]) W^-k / 2.
+template <int NY, int NX, int RPB, typename C>
+__device__ __forceinline__ void inverse_rows(const C* __restrict__ Tf, C* buf, const C* tw) {
+  using R = real_t<C>;
+  constexpr int L = NX / 2, H = NX / 2 + 1, LS = lds_len(L) + 1;
+  const unsigned tid = threadIdx.x;
+  // column-major T: column k holds rows y0..y0+RPB-1 consecutively; all loads
+  // before the first use
+  {
+    constexpr int IT = (RPB * H + kThreads - 1) / kThreads;
+    C in[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * H - 1));
+      in[it] = Tf[(size_t)(i / RPB) * NY + i % RPB];
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      if ((RPB * H) % kThreads == 0 || i < (unsigned)(RPB * H)) buf[i % RPB * LS + i / RPB] = in[it];
+    }
+  }
+  __syncthreads();
+  const R half = R(0.5);
+  {
+    constexpr int IT = (RPB * L + kThreads - 1) / kThreads;
+    C zp[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * L - 1));
+      const unsigned r = i / L, k = i % L;
+      const C xk = buf[r * LS + k];
+      const C xc = cconj(buf[r * LS + L - k]);
+      const C e = cscale(cadd(xk, xc), half);
+      const C o = cmul(cscale(csub(xk, xc), half), cconj(tw[k]));
+      zp[it] = mkc<C>(e.x - o.y, e.y + o.x);  // e + i o
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const unsigned i = tid + it * kThreads;
+      if ((RPB * L) % kThreads == 0 || i < (unsigned)(RPB * L)) buf[i / L * LS + lds_idx(i % L)] = zp[it];
+    }
+  }
+  __syncthreads();
+  fft_lds<L, +1, NX, RPB, kThreads>(buf, RPB, LS, tw);
+}
+
 // Row pass, forward.  weight: 0 A = I, 1 B = -1/(E+eps), 2 A = (I+eps)^2.
 // Writes T[f][k][y] (column-major), k < NX/2+1.  With st != null records
 // min/max of A (as FP32 keys) and non-finite pixels per frame.  C = float2
@@ -211,21 +282,7 @@ __global__ void __launch_bounds__(kThreads) k_rows_fwd(ImgSrc src, int weight, d
     if (bad) atomicOr(&st[f].flags, (unsigned)CCPT_ST_NONFINITE);
   }
   fft_lds<L, -1, NX, RPB, kThreads>(buf, RPB, LS, tw);
-  const C* z = buf;
-  // unpack: X[k] = E[k] + W^k O[k], E = (Z[k] + conj Z[L-k]) / 2,
-  // O = (Z[k] - conj Z[L-k]) / (2i), W = exp(-2 pi i / NX); stored column-major
-  // T[k][y] so each column k receives RPB consecutive rows
-  C* Tf = T + (size_t)f * NY * H;
-  const R half = R(0.5);
-  for (unsigned i = tid; i < (unsigned)(RPB * H); i += kThreads) {
-    const unsigned k = i / RPB, r = i % RPB;
-    const C zk = z[r * LS + lds_idx(k == L ? 0 : k)];
-    const C zc = cconj(z[r * LS + lds_idx(k == 0 ? 0 : L - k)]);
-    const C e = cscale(cadd(zk, zc), half);
-    const C d = csub(zk, zc);
-    const C o = mkc<C>(half * d.y, -half * d.x);  // d / (2i)
-    Tf[(size_t)k * NY + y0 + r] = cadd(e, cmul(tw[k], o));
-  }
+  unpack_rows<NY, NX, RPB>(buf, tw, T + (size_t)f * NY * H, y0);
 }
 
 enum ColKind { COL_XCORR = 0, COL_FWD = 1, COL_FWD_CONJ = 2, COL_INV = 3 };
@@ -366,10 +423,7 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
   }
 }
 
-// Row pass, inverse (c2r).  Each row's NX/2+1 bins are packed into NX/2
-// complex values Z = E + i O with E = (X[k] + conj X[L-k]) / 2 and
-// O = (X[k] - conj X[L-k]) W^-k / 2, transformed, and read out as the NX
-// reals z[n] = a[2n] + i a[2n+1].
+// Row pass, inverse (c2r): rows come out as the NX reals z[n] = a[2n] + i a[2n+1].
 // ARGMAX: per-frame maximum with ties to the lowest row-major index of the
 // frame (trans: of the wide frame, whose row-major order is the tall image's
 // column-major order): in FP32 one 64-bit atomic key per frame, in FP64 one
@@ -394,53 +448,13 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   const int f = blockIdx.y;
   const int y0 = blockIdx.x * RPB;
   for (unsigned i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
-  // column-major T: column k holds rows y0..y0+RPB-1 consecutively; all loads
-  // before the first use
-  const C* Tf = T + (size_t)f * NY * H + y0;
-  {
-    constexpr int IT = (RPB * H + kThreads - 1) / kThreads;
-    C in[IT];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * H - 1));
-      in[it] = Tf[(size_t)(i / RPB) * NY + i % RPB];
-    }
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const unsigned i = tid + it * kThreads;
-      if ((RPB * H) % kThreads == 0 || i < (unsigned)(RPB * H)) buf[i % RPB * LS + i / RPB] = in[it];
-    }
-  }
+  inverse_rows<NY, NX, RPB>(T + (size_t)f * NY * H + y0, buf, tw);
   // frame row-major index of tall pixel (y, x), and the step to (y, x + 1)
   const bool trans = transposed<NY, NX>(trans_in);
   auto flat_of = [&](int y, int x) {
     return trans ? (unsigned)(x * NY + y) : (unsigned)(y * NX + x);
   };
   const unsigned xstep = trans ? (unsigned)NY : 1u;
-  __syncthreads();
-  const R half = R(0.5);
-  {
-    constexpr int IT = (RPB * L + kThreads - 1) / kThreads;
-    C zp[IT];
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const unsigned i = min(tid + it * kThreads, (unsigned)(RPB * L - 1));
-      const unsigned r = i / L, k = i % L;
-      const C xk = buf[r * LS + k];
-      const C xc = cconj(buf[r * LS + L - k]);
-      const C e = cscale(cadd(xk, xc), half);
-      const C o = cmul(cscale(csub(xk, xc), half), cconj(tw[k]));
-      zp[it] = mkc<C>(e.x - o.y, e.y + o.x);  // e + i o
-    }
-    __syncthreads();
-#pragma unroll
-    for (int it = 0; it < IT; ++it) {
-      const unsigned i = tid + it * kThreads;
-      if ((RPB * L) % kThreads == 0 || i < (unsigned)(RPB * L)) buf[i / L * LS + lds_idx(i % L)] = zp[it];
-    }
-  }
-  __syncthreads();
-  fft_lds<L, +1, NX, RPB, kThreads>(buf, RPB, LS, tw);
   const C* z = buf;
   if constexpr (ARGMAX && !FP64) {
     // the two largest values of the block (equal ones count twice), then the
@@ -558,6 +572,123 @@ __global__ void __launch_bounds__(kThreads) k_rows_inv(const C* __restrict__ T, 
   }
 }
 
+// Real-time reference update (Eq. 9) by one frame, the column pass: forward FFT
+// of the frame's columns (T), v = F phi_ky(d_y) phi_kx(d_x) (the frame shifted
+// back), the resident spectrum S <- a0 v + b1 S (conj_s: conj v; a frame that
+// did not track leaves S as it is) and, INV, the inverse FFT of S's columns back
+// into T.  One kernel where the passes took three; a single frame waits for
+// launches and latency only (the CC-SN call of 256 x 128 frames, tracking and
+// update: 69 us -> 63 with k_rows_update; bits as before).
+template <int NY, int NX, int CB, bool INV>
+__global__ void __launch_bounds__(kThreads) k_cols_update(const ccpt_result* __restrict__ res,
+                                                          float2* __restrict__ T, float2* __restrict__ spec,
+                                                          float a0, float b1, int conj_s, int trans,
+                                                          const float2* __restrict__ gtw) {
+  constexpr int H = NX / 2 + 1, S = lds_len(NY) + 1, NC = NX / 2, CS = CB + 1;
+  __shared__ float2 tw[NY];
+  __shared__ float2 buf[CS * S];
+  __shared__ float2 px[CS], py[NY];
+  const unsigned tid = threadIdx.x;
+  const int c0 = blockIdx.x * CB;
+  const int nreg = min(CB, NC - c0);
+  const bool has_nyq = blockIdx.x == 0;
+  const int nseq = has_nyq ? CS : CB;
+  auto col_of = [&](int c) { return c < nreg ? c0 + c : (c == CB && has_nyq ? NC : -1); };
+  const ccpt_result r = *res;
+  const bool ok = tracked(r);
+  if (!INV && !ok) return;
+  for (unsigned i = tid; i < NY; i += kThreads) tw[i] = gtw[i];
+  constexpr int IT = (NY * CS + kThreads - 1) / kThreads;
+  const unsigned count = (unsigned)(NY * nseq);
+  float2 in[IT], old[IT];
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const unsigned i = min(tid + it * kThreads, count - 1);
+    const int kx = max(col_of(i / NY), 0);
+    in[it] = T[(size_t)kx * NY + i % NY];
+  }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const unsigned i = min(tid + it * kThreads, count - 1);
+    const unsigned y = has_nyq ? i / CS : i / CB, c = has_nyq ? i % CS : i % CB;
+    old[it] = spec[(size_t)y * H + max(col_of(c), 0)];
+  }
+  const double dy = trans ? r.d[1] : r.d[0], dx = trans ? r.d[0] : r.d[1];
+  for (unsigned k = tid; ok && k < NY + CS; k += kThreads) {
+    if (k < NY)
+      py[k] = shift_phase(k, NY, dy);
+    else if (col_of(k - NY) >= 0)
+      px[k - NY] = shift_phase(col_of(k - NY), NX, dx);
+  }
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const unsigned i = tid + it * kThreads;
+    if (i < count) {
+      const bool c_ok = col_of(i / NY) >= 0;
+      buf[i / NY * S + lds_idx(i % NY)] = make_float2(c_ok ? in[it].x : 0, c_ok ? in[it].y : 0);
+    }
+  }
+  __syncthreads();
+  fft_lds<NY, -1, NY, CS, kThreads>(buf, nseq, S, tw);
+#pragma unroll
+  for (int it = 0; it < IT; ++it) {
+    const unsigned i = tid + it * kThreads;
+    const unsigned y = has_nyq ? i / CS : i / CB, c = has_nyq ? i % CS : i % CB;
+    if (i < count) {
+      const int kx = col_of(c);
+      float2 n = make_float2(0.f, 0.f);
+      if (kx >= 0) {
+        n = old[it];
+        if (ok) {
+          float2 v = cmul(buf[c * S + lds_idx(y)], cmul(py[y], px[c]));
+          if (conj_s) v = cconj(v);
+          n = make_float2(a0 * v.x + b1 * n.x, a0 * v.y + b1 * n.y);
+          spec[(size_t)y * H + kx] = n;
+        }
+      }
+      if (INV) buf[c * S + lds_idx(y)] = n;
+    }
+  }
+  if constexpr (INV) {
+    __syncthreads();
+    fft_lds<NY, +1, NY, CS, kThreads>(buf, nseq, S, tw);
+    for (unsigned i = tid; i < (unsigned)(NY * nseq); i += kThreads) {
+      const unsigned c = i / NY, y = i % NY;
+      const int kx = col_of(c);
+      if (kx >= 0) T[(size_t)kx * NY + y] = buf[c * S + lds_idx(y)];
+    }
+  }
+}
+
+// Real-time CC-SN update, the row pass: rows inverse to the updated E (stored to
+// img unless null), B = -1/(E+eps), rows forward, T in place.
+template <int NY, int NX, int RPB>
+__global__ void __launch_bounds__(kThreads) k_rows_update(float2* __restrict__ T, float* __restrict__ img,
+                                                          float scale, float eps,
+                                                          const float2* __restrict__ gtw) {
+  constexpr int L = NX / 2, LS = lds_len(L) + 1;
+  __shared__ float2 tw[NX];
+  __shared__ float2 buf[RPB * LS];
+  const unsigned tid = threadIdx.x;
+  const int y0 = blockIdx.x * RPB;
+  for (unsigned i = tid; i < NX; i += kThreads) tw[i] = gtw[i * (NY / NX)];
+  inverse_rows<NY, NX, RPB>((const float2*)T + y0, buf, tw);
+  for (unsigned i = tid; i < (unsigned)(RPB * L); i += kThreads) {
+    const unsigned r = i / L, n = i % L;
+    float2& z = buf[r * LS + lds_idx(n)];
+    float a = z.x * scale, b = z.y * scale;
+    asm volatile("" : "+v"(a), "+v"(b));  // E is rounded before eps is added
+    if (img) {
+      img[(size_t)(y0 + r) * NX + 2 * n] = a;
+      img[(size_t)(y0 + r) * NX + 2 * n + 1] = b;
+    }
+    z = make_float2(-1.0f / (a + eps), -1.0f / (b + eps));
+  }
+  __syncthreads();
+  fft_lds<L, -1, NX, RPB, kThreads>(buf, RPB, LS, tw);
+  unpack_rows<NY, NX, RPB>(buf, tw, T, y0);
+}
+
 template <int NY, int NX>
 static int xcorr_n(const GroupParams& g, hipStream_t s, const Marker& mark) {
   constexpr int RPB = row_block(NY, NX);
@@ -619,36 +750,76 @@ static int spectrum_n(const void* data, int dtype, int pitch, long img_stride, i
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Spectra of frames given by descriptors, held tall (trans: the frames are
-// wide and read transposed): T and spec as in the tracking passes.
-template <int NY, int NX>
-static int frame_spectra_n(const FrameDesc* desc, int first, int count, int mode, float eps,
-                           int trans, float2* T, float2* spec, const float2* tw, hipStream_t s) {
-  constexpr int RPB = row_block(NY, NX);
-  constexpr int CB = cols_per_block(NY, NX);
-  constexpr int H = NX / 2 + 1;
-  ImgSrc src{desc, first, nullptr, 0, 0, 0, trans};
-  hipLaunchKernelGGL((k_rows_fwd<NY, NX, RPB, float2>), dim3(NY / RPB, count), dim3(kThreads), 0,
-                     s, src, mode == CCPT_MODE_CCSN ? 2 : 0, (double)eps, T, (FrameState*)nullptr,
-                     tw);
-  hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_FWD, float2>), dim3((NX / 2 + CB - 1) / CB, count),
-                     dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (float2*)nullptr, spec, (long)NY * H, tw);
+// Spectra of frames given by descriptors.
+template <int N>
+static int frame_spectra_n(const FrameDesc* desc, int first, int count, int mode, float eps, float2* T,
+                           float2* spec, const float2* tw, hipStream_t s) {
+  constexpr int RPB = row_block(N, N);
+  constexpr int CB = cols_per_block(N, N);
+  constexpr int H = N / 2 + 1;
+  ImgSrc src{desc, first, nullptr, 0, 0, 0, 0};
+  hipLaunchKernelGGL((k_rows_fwd<N, N, RPB, float2>), dim3(N / RPB, count), dim3(kThreads), 0, s, src,
+                     mode == CCPT_MODE_CCSN ? 2 : 0, (double)eps, T, (FrameState*)nullptr, tw);
+  hipLaunchKernelGGL((k_cols<N, N, CB, COL_FWD, float2>), dim3((N / 2 + CB - 1) / CB, count), dim3(kThreads), 0, s,
+                     (const FrameDesc*)nullptr, 0, T, (float2*)nullptr, spec, (long)N * H, tw);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// Real images (NY rows of NX, the tall layout) from half spectra.
+// Real images from half spectra.
+template <int N>
+static int inverse_n(const float2* spec, int n, float scale, float2* T, float* img, const float2* tw,
+                     hipStream_t s) {
+  constexpr int RPB = row_block(N, N);
+  constexpr int CB = cols_per_block(N, N);
+  constexpr int H = N / 2 + 1;
+  hipLaunchKernelGGL((k_cols<N, N, CB, COL_INV, float2>), dim3((N / 2 + CB - 1) / CB, n), dim3(kThreads), 0, s,
+                     (const FrameDesc*)nullptr, 0, T, (float2*)nullptr, (float2*)spec, (long)N * H, tw);
+  hipLaunchKernelGGL((k_rows_inv<N, N, RPB, false, float2>), dim3(N / RPB, n), dim3(kThreads), 0, s, T,
+                     (FrameState*)nullptr, img, scale, tw, (PeakCand*)nullptr, 0);
+  return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+// Frame (descriptor 0) -> T, then the update of `S`; CC-SN: E and conj F[B].
 template <int NY, int NX>
-static int inverse_n(const float2* spec, int n, float scale, float2* T, float* img,
-                     const float2* tw, hipStream_t s) {
+static int rt_update_n(const RtUpdate& u, int trans, hipStream_t s) {
   constexpr int RPB = row_block(NY, NX);
   constexpr int CB = cols_per_block(NY, NX);
   constexpr int H = NX / 2 + 1;
-  hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_INV, float2>), dim3((NX / 2 + CB - 1) / CB, n),
-                     dim3(kThreads), 0, s, (const FrameDesc*)nullptr, 0, T, (float2*)nullptr,
-                     (float2*)spec, (long)NY * H, tw);
-  hipLaunchKernelGGL((k_rows_inv<NY, NX, RPB, false, float2>), dim3(NY / RPB, n), dim3(kThreads), 0,
-                     s, T, (FrameState*)nullptr, img, scale, tw, (PeakCand*)nullptr, 0);
+  const dim3 rows(NY / RPB, 1), cols((NX / 2 + CB - 1) / CB, 1);
+  ImgSrc src{u.desc, 0, nullptr, 0, 0, 0, trans};
+  hipLaunchKernelGGL((k_rows_fwd<NY, NX, RPB, float2>), rows, dim3(kThreads), 0, s, src, 0, 0.0, u.T,
+                     (FrameState*)nullptr, u.tw);
+  if (!u.espec) {
+    hipLaunchKernelGGL((k_cols_update<NY, NX, CB, false>), cols, dim3(kThreads), 0, s, u.res, u.T, u.rspec, u.a0,
+                       u.b1, 1, trans, u.tw);
+  } else {
+    hipLaunchKernelGGL((k_cols_update<NY, NX, CB, true>), cols, dim3(kThreads), 0, s, u.res, u.T, u.espec, u.a0,
+                       u.b1, 0, trans, u.tw);
+    // the row pass of the inverse returns half the unnormalised transform
+    hipLaunchKernelGGL((k_rows_update<NY, NX, RPB>), rows, dim3(kThreads), 0, s, u.T, u.img,
+                       2.0f / ((float)NY * (float)NX), u.eps, u.tw);
+    hipLaunchKernelGGL((k_cols<NY, NX, CB, COL_FWD_CONJ, float2>), cols, dim3(kThreads), 0, s,
+                       (const FrameDesc*)nullptr, 0, u.T, (float2*)nullptr, u.rspec, (long)NY * H, u.tw);
+  }
   return hipGetLastError() == hipSuccess ? 0 : -1;
+}
+
+int launch_rt_update(int ny, int nx, int trans, const RtUpdate& u, hipStream_t s) {
+  if (ny == nx) {
+    switch (ny) {
+#define CASE(n) \
+  case n:       \
+    return rt_update_n<n, n>(u, 0, s);
+      CCPT_FOR_SIZES(CASE)
+#undef CASE
+    }
+    return -2;
+  }
+#define CASE(a, b) \
+  if (ny == a && nx == b) return rt_update_n<a, b>(u, trans, s);
+  CCPT_FOR_RECT(CASE)
+#undef CASE
+  return -2;
 }
 
 int launch_xcorr(int ny, int nx, const GroupParams& g0, hipStream_t s, const Marker& mark) {
@@ -747,42 +918,27 @@ int launch_spectrum64(int N, const void* data, int dtype, int pitch, long img_st
   return -2;
 }
 
-int launch_frame_spectra(int ny, int nx, int trans, const FrameDesc* desc, int first, int count,
-                         int mode, float eps, float2* T, float2* spec, const float2* tw,
-                         hipStream_t s) {
-  if (ny == nx) {
-    switch (ny) {
-#define CASE(nn) \
-  case nn:       \
-    return frame_spectra_n<nn, nn>(desc, first, count, mode, eps, 0, T, spec, tw, s);
-      CCPT_FOR_SIZES(CASE)
+int launch_frame_spectra(int N, const FrameDesc* desc, int first, int count, int mode, float eps, float2* T,
+                         float2* spec, const float2* tw, hipStream_t s) {
+  switch (N) {
+#define CASE(n) \
+  case n:       \
+    return frame_spectra_n<n>(desc, first, count, mode, eps, T, spec, tw, s);
+    CCPT_FOR_SIZES(CASE)
 #undef CASE
-    }
-    return -2;
   }
-#define CASE(a, b) \
-  if (ny == a && nx == b) return frame_spectra_n<a, b>(desc, first, count, mode, eps, trans, T, spec, tw, s);
-  CCPT_FOR_RECT(CASE)
-#undef CASE
   return -2;
 }
 
-int launch_inverse(int ny, int nx, const float2* spec, int n, float scale, float2* T, float* img,
-                   const float2* tw, hipStream_t s) {
-  if (ny == nx) {
-    switch (ny) {
+int launch_inverse(int N, const float2* spec, int n, float scale, float2* T, float* img, const float2* tw,
+                   hipStream_t s) {
+  switch (N) {
 #define CASE(nn) \
   case nn:       \
-    return inverse_n<nn, nn>(spec, n, scale, T, img, tw, s);
-      CCPT_FOR_SIZES(CASE)
+    return inverse_n<nn>(spec, n, scale, T, img, tw, s);
+    CCPT_FOR_SIZES(CASE)
 #undef CASE
-    }
-    return -2;
   }
-#define CASE(a, b) \
-  if (ny == a && nx == b) return inverse_n<a, b>(spec, n, scale, T, img, tw, s);
-  CCPT_FOR_RECT(CASE)
-#undef CASE
   return -2;
 }
 

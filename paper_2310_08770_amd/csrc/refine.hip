@@ -107,7 +107,11 @@ __device__ unsigned peak_of_cands(const PeakCand* cd, int nb, bool& tie) {
 //
 // The pass is meant to be bound by reading X once (264 KB per 256 x 256
 // frame): the next kDepth - 1 k steps' loads are in flight while one is
-// summed.
+// summed.  10,000 frames of 256 x 256 take 1.11 ms (2.4 TB/s of the 5.2 that a
+// copy reaches; the FP64 matrix instructions alone would take 0.45 ms); other
+// depths, three blocks per CU and one tile per wave were within 3 %.  With
+// k_window_max it replaces the matrix DFT (1.6 ms on 16-bit operands, 7.3 ms in
+// FP32) and Newton's own passes over X (0.8 ms).
 template <typename CX, int TPW>
 struct CoefStep {
   CX a[TPW], b[TPW];
@@ -483,6 +487,10 @@ constexpr int kMaxPasses = 3;
 // lane.  c is scaled by a power of two and its constant
 // (the largest term, which moves no maximum) is dropped before the rounding
 // to FP32.  The FP64 mode does the same with 24 terms on 16x16x4 FP64.
+// Bound by the serial chain of a frame (coefficients, grid, maximum, Newton's
+// FP64 steps), not by the grid's matrix work: 10,000 frames of 256 x 256, u =
+// 100, take 0.68 ms; one frame takes 14 us, against 26 us for the second half of
+// the DFT and Newton before.
 template <typename CX>
 __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 2)
     k_window_max(GroupParams g, WindowTables t, int ny, int nx, int nparts, int nb, double step_limit) {

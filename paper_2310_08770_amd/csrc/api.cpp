@@ -1203,17 +1203,27 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
     aoff[r] = ao;
     ao += (long)spec_elems(nn);
   }
-  // workspace per frame: F[A], QA, QB, T spectra and one image
-  auto per_frame = [](int nn) { return 4 * spec_elems(nn) * sizeof(float2) + (size_t)nn * nn * 4; };
+  // Workspace: QB of a chunk's frames, and T, F[A], QA and an image of those that
+  // the passes take: all, or where frames fit LDS at most a short last round (so
+  // that 1024 frames of 128 x 128 are one launch; in launches of 795 and 229, with
+  // room for the passes of all, the adjoint took 165 us instead of 136).
   const size_t budget = (size_t)256 << 20;
+  auto in_lds = [](int nn) { return lds_frames(nn, nn, kLdsRound) > 0; };
+  auto qb_bytes = [](int nn) { return spec_elems(nn) * sizeof(float2); };
+  auto pass_bytes = [](int nn) { return 3 * spec_elems(nn) * sizeof(float2) + (size_t)nn * nn * 4; };
+  auto chunk_of = [&](int nn, int cnt) {
+    const size_t fit = in_lds(nn) ? (budget - pass_bytes(nn) * (kGradMinFrames - 1)) / qb_bytes(nn)
+                                  : budget / (qb_bytes(nn) + pass_bytes(nn));
+    return std::max(1, (int)std::min<size_t>({(size_t)cnt, fit, (size_t)65535}));  // (a grid's y)
+  };
+  auto pass_frames = [&](int nn, int chunk) { return in_lds(nn) ? std::min(chunk, kGradMinFrames - 1) : chunk; };
   size_t ws_need = 0, img_need = 0;
   for (size_t gi = 0; gi < plan.sig.size(); gi += 2) {
-    const int nn = plan.sig[gi], cnt = plan.sig[gi + 1];
-    const int chunk = std::max(1, std::min<int>(cnt, (int)(budget / per_frame(nn))));
-    ws_need = std::max(ws_need, per_frame(nn) * chunk + 256);
+    const int nn = plan.sig[gi], chunk = chunk_of(nn, plan.sig[gi + 1]);
+    ws_need = std::max(ws_need, qb_bytes(nn) * chunk + pass_bytes(nn) * pass_frames(nn, chunk) + 256);
   }
   for (int r = 0; r < nrefs; ++r)
-    img_need = std::max(img_need, per_frame(ctx->refs[r].n) + 256);
+    img_need = std::max(img_need, pass_bytes(ctx->refs[r].n) + 256);
   rc = ensure_ws(ctx, std::max(ws_need, img_need));
   if (rc) return rc;
   // frames of each chunk by reference, in runs (the sums of the reference gradients)
@@ -1228,7 +1238,7 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
     int first = 0;
     for (size_t gi = 0; gi < plan.sig.size(); gi += 2) {
       const int nn = plan.sig[gi], cnt = plan.sig[gi + 1];
-      const int chunk = std::max(1, std::min<int>(cnt, (int)(budget / per_frame(nn))));
+      const int chunk = chunk_of(nn, cnt);
       for (int c0 = 0; c0 < cnt; c0 += chunk) {
         const int count = std::min(chunk, cnt - c0);
         const FrameDesc* d = plan.desc.data() + first + c0;
@@ -1297,16 +1307,17 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
   mark(CCPT_STAGE_GRAD, 1);
   for (size_t gi = 0; gi < plan.sig.size(); gi += 2) {
     const int nn = plan.sig[gi], cnt = plan.sig[gi + 1];
-    const int chunk = std::max(1, std::min<int>(cnt, (int)(budget / per_frame(nn))));
+    const int chunk = chunk_of(nn, cnt);
     const float2* tw = ctx->tables[nn].tw;
     const size_t spec = spec_elems(nn);
     for (int c0 = 0; c0 < cnt; c0 += chunk) {
       const int count = std::min(chunk, cnt - c0);
-      float2* T = (float2*)ctx->ws;
-      float2* FA = T + spec * chunk;
-      float2* QA = FA + spec * chunk;
-      float2* QB = QA + spec * chunk;
-      float* img = (float*)(QB + spec * chunk);
+      const size_t pf = pass_frames(nn, chunk);
+      float2* QB = (float2*)ctx->ws;
+      float2* T = QB + spec * chunk;
+      float2* FA = T + spec * pf;
+      float2* QA = FA + spec * pf;
+      float* img = (float*)(QA + spec * pf);
       const int f0 = first + c0;
       GradParams g{ctx->d_desc, f0, count, fwd, g_d, g_peak, g_ref ? QB : nullptr, d_goff, g_frames, mode, eps, tw};
       // frames that fit LDS in one kernel, the others in passes

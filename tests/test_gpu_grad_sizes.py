@@ -65,9 +65,11 @@ def test_sizes_that_8_does_not_divide(n):
 @pytest.mark.parametrize("n,count,nrefs,runs", [
     (16, 1, 1, False), (24, 17, 1, False), (54, 16, 2, False), (64, 67, 3, True),
     (128, 33, 2, True), (128, 33, 2, False), (144, 130, 1, False), (192, 3, 1, False),
-    (192, 129, 2, True), (162, 258, 1, False), (256, 18, 1, False)])
+    (192, 129, 2, True), (162, 258, 1, False), (256, 18, 1, False),
+    (512, 31, 2, False)])
 def test_runs_and_rounds(n, count, nrefs, runs, mode):
     # one frame; a run and one more; references in turn (runs of 8 and 9) and in
-    # runs; a launch of the one-kernel path, of the passes, and of both
+    # runs; a launch of the one-kernel path, of the passes, and of both; frames
+    # that fill more than one chunk of the workspace
     print(f"case: adjoint {n}x{n}, {count} frames, {nrefs} references, {mode}", flush=True)
     check(n, count, nrefs, mode, runs)

@@ -124,6 +124,7 @@ struct ccpt_ctx {
   hipStream_t cur_stream = nullptr;
   hipEvent_t open_ev = nullptr;
   // adjoint: packed-gradient offsets + accumulator pointers, accumulators
+  size_t ws_refused = ~(size_t)0;  // a workspace that the card had no room for
   void* gsmall = nullptr;
   size_t gsmall_cap = 0;
   char* h_small = nullptr;
@@ -1036,14 +1037,20 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
       ost[l + 1] = ost[l] + lst[l] * nslots;
     }
   };
-  // a card with no room for the launches' workspace takes smaller ones
-  bool small = false;
-  layout(small);
-  rc = ensure_ws(ctx, ows[nl]);
-  if (rc == CCPT_E_NOMEM) {
-    (void)hipGetLastError();  // the refused allocation is not a launch's error
-    small = true;
-    layout(small);
+  // a card with no room for the launches' workspace takes smaller ones, from then
+  // on without asking again (asking gives up the workspace in hand)
+  layout(false);
+  bool small = ows[nl] >= ctx->ws_refused;
+  if (!small) {
+    rc = ensure_ws(ctx, ows[nl]);
+    if (rc == CCPT_E_NOMEM) {
+      (void)hipGetLastError();  // the refused allocation is not a launch's error
+      ctx->ws_refused = ows[nl];
+      small = true;
+    }
+  }
+  if (small) {
+    layout(true);
     rc = ensure_ws(ctx, ows[nl]);
   }
   if (rc) return rc;

@@ -81,12 +81,16 @@ struct Schedule {
 // Size groups of one call run concurrently on up to kMaxLanes streams.
 constexpr int kMaxLanes = 4;
 
+// What decides the launches of a call, and the addresses they hold, beside the
+// context's own (whose changes drop the graphs).
 struct GraphKey {
-  std::vector<int> sig;  // group sizes and counts
+  std::vector<int> sig;     // group sizes and counts
+  std::vector<char> pairs;  // by group: which correlation its pixels allow
+  bool small;               // launches of what fits 192 MB
   const void* out;
   hipStream_t stream;
   bool operator<(const GraphKey& o) const {
-    return std::tie(sig, out, stream) < std::tie(o.sig, o.out, o.stream);
+    return std::tie(sig, pairs, small, out, stream) < std::tie(o.sig, o.pairs, o.small, o.out, o.stream);
   }
 };
 
@@ -1061,9 +1065,12 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   rc = upload_desc(ctx, plan.desc, s);
   if (rc) return rc;
 
+  std::vector<int> first(ngroups, 0);
+  for (int gi = 1; gi < ngroups; ++gi) first[gi] = first[gi - 1] + sig[2 * gi - 1];
+  std::vector<char> pairs(ngroups);
+  for (int gi = 0; gi < ngroups; ++gi) pairs[gi] = pairs_ok(plan.desc, first[gi], sig[2 * gi + 1]);
+
   auto launch_all = [&]() -> int {
-    std::vector<int> first(ngroups, 0);
-    for (int gi = 1; gi < ngroups; ++gi) first[gi] = first[gi - 1] + sig[2 * gi - 1];
     // lanes 1.. start after everything already queued on the caller's stream
     if (nl > 1) {
       HIP_CHECK(ctx, hipEventRecord(ctx->fork_evt, s));
@@ -1082,8 +1089,7 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
       for (int gi = 0; gi < ngroups && r2 == CCPT_OK; ++gi) {
         if (lane_of[gi] != l) continue;
         const int nn = sig[2 * gi], cnt = sig[2 * gi + 1];
-        r2 = run_group(ctx, mem, nn, ctx->d_desc, first[gi], cnt, out, ls,
-                       pairs_ok(plan.desc, first[gi], cnt));
+        r2 = run_group(ctx, mem, nn, ctx->d_desc, first[gi], cnt, out, ls, pairs[gi]);
       }
     }
     // every lane that was forked joins back, also after a failed launch
@@ -1100,7 +1106,7 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   const bool use_graph = (ctx->o.flags & CCPT_FLAG_GRAPH) && !(ctx->o.flags & CCPT_FLAG_PROFILE) &&
                          s != nullptr;
   if (!use_graph) return launch_all();
-  GraphKey key{sig, out, s};
+  GraphKey key{sig, pairs, small, out, s};
   auto it = ctx->graphs.find(key);
   if (it == ctx->graphs.end()) {
     hipGraph_t graph;

@@ -43,6 +43,14 @@ template <typename C>
 __device__ __forceinline__ C cmul(C a, C b) {
   return mkc<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+// The same with its roundings fixed: left to the compiler, which product of a sum
+// is fused depends on the code around it, and the kernels that form the
+// cross-power spectrum have to agree (blocks of one value a thread, 16 x 16 to 24 x
+// 24, had the products of y the other way round in the column pass).
+template <typename C>
+__device__ __forceinline__ C cmul_fixed(C a, C b) {
+  return mkc<C>(fma(a.x, b.x, -(a.y * b.y)), fma(a.y, b.x, a.x * b.y));
+}
 template <typename C>
 __device__ __forceinline__ C cconj(C a) { return mkc<C>(a.x, -a.y); }
 template <typename C>

@@ -411,7 +411,7 @@ __global__ void __launch_bounds__(kThreads) k_cols(const FrameDesc* __restrict__
         if (i < count) {
           C v = zero;
           if (kx >= 0) {
-            v = cmul(r[c * S + lds_idx(y)], rv[it]);
+            v = cmul_fixed(r[c * S + lds_idx(y)], rv[it]);
             Xf[(size_t)y * H + kx] = v;
           }
           r[c * S + lds_idx(y)] = v;

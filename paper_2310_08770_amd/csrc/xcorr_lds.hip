@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(lds_threads(NY, NX)) k_xcorr_lds(GroupParams g
         const unsigned i = i0 + e * THR;
         if (i < NY * H) {
           const unsigned y = i / H, kx = i % H;
-          const float2 v = cmul(m[at<NY, false>(kx, y)], r[e]);
+          const float2 v = cmul_fixed(m[at<NY, false>(kx, y)], r[e]);
           Xf[i] = v;
           m[at<NY, false>(kx, y)] = v;
         }

@@ -325,7 +325,9 @@ int ccpt_drift_filter(const double* r, int n, double a0, double rate_limit, doub
 int ccpt_autotune(ccpt_ctx* ctx, int n, int batch, void* stream);
 
 /* Reads (set = 0) or sets (set != 0) the chunk size used for frames of size
-   n x n; 0 restores the default.  Lets a caller persist tuning results. */
+   n x n; 0 restores the default.  Lets a caller persist tuning results: with no
+   chunk set the most frames of a default launch are read, and setting that
+   number is setting the default. */
 int ccpt_schedule(ccpt_ctx* ctx, int n, int* chunk, int set);
 
 /* Launch plan of one frame shape (a10), any supported ny x nx (rectangles
@@ -333,7 +335,8 @@ int ccpt_schedule(ccpt_ctx* ctx, int n, int* chunk, int set);
    Tuning it changes how work is split over blocks and launches, never the
    arithmetic of a launch of a given size. */
 typedef struct ccpt_plan {
-  int chunk;        /* frames per launch chunk; 0 = default */
+  int chunk;        /* frames per launch chunk; 0 (or the value read where none is
+                       set, the most frames of a default launch) = default */
   int split_blocks; /* launches of fewer than this many frames spread each frame's window
                        expansion over several blocks, added in a fixed order
                        (latency); -1 = default (128), 0 = never; at most 512 */

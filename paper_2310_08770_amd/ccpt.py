@@ -379,7 +379,7 @@ class Tracker:
         return chunk
 
     def chunk(self, n):
-        """Frames per launch chunk currently used for n x n frames."""
+        """Most frames per launch currently used for n x n frames."""
         c = c_int(0)
         self._check(lib().ccpt_schedule(self._h, int(n), ctypes.byref(c), 0))
         return c.value

@@ -330,14 +330,27 @@ int default_chunk(int n, int precision) {
   return std::max(unit_frames(n, precision), (int)std::min<size_t>(768, cap));
 }
 
+// The most frames that a default launch takes (launches()): the chunk that is
+// reported where none is set.
+int default_most(int n, int precision) {
+  const int c = default_chunk(n, precision);
+  return c + c / 4;
+}
+
+// The chunk that a plan sets, 0 for the default launches.  The reported value of
+// the default stands for the default: a plan that is read and written back, or
+// kept and restored, changes no launch (chunks of that many frames taken as they
+// are would end in other launches, give other frames the one-kernel correlation
+// and have no smaller ones to fall back to).
 int set_chunk(const ccpt_ctx* ctx, int n) {
   auto it = ctx->sched.find(n);
-  return it != ctx->sched.end() && it->second.chunk > 0 ? it->second.chunk : 0;
+  const int c = it != ctx->sched.end() ? it->second.chunk : 0;
+  return c > 0 && c != default_most(n, ctx->o.precision) ? c : 0;
 }
 
 int chunk_for(const ccpt_ctx* ctx, int n) {
   const int c = set_chunk(ctx, n);
-  return c > 0 ? c : default_chunk(n, ctx->o.precision);
+  return c > 0 ? c : default_most(n, ctx->o.precision);
 }
 
 int split_blocks_for(const ccpt_ctx* ctx, int n) {
@@ -389,7 +402,7 @@ std::vector<Launch> launches(const ccpt_ctx* ctx, int n, int count, bool small, 
   const int chunk = default_chunk(n, ctx->o.precision);
   auto split = [&](int left, int f) {
     while (left > 0) {
-      const int c = left <= chunk + chunk / 4 ? left : chunk;
+      const int c = left <= default_most(n, ctx->o.precision) ? left : chunk;
       v.push_back(Launch{c, f});
       left -= c;
     }

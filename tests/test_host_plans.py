@@ -1,0 +1,29 @@
+"""Launch plans and the tuners, by the launches that they lead to."""
+import pytest
+import torch
+
+from tests._host import host, host_lib  # noqa: F401
+
+
+def run(host, tr, count, n, dtype=torch.float32):
+    frame = torch.zeros(n, n, dtype=dtype)
+    tr.track([frame] * count, [0] * count, stream=0)
+    return host.launches()
+
+
+@pytest.mark.parametrize("n", [16, 64, 256, 512])
+@pytest.mark.parametrize("precision", ["fp32", "bf16x2", "fp64"])
+def test_a_plan_that_is_read_and_written_back_changes_nothing(host, n, precision):
+    tr = host.tracker(precision=precision)
+    tr.set_reference(torch.ones(n, n), stream=0)
+    counts = (1, 100, 481, 762, 961, 1500, 6000)  # 481 frames of 256 x 256: 381 in one kernel, 100 in passes
+    want = [run(host, tr, c, n) for c in counts]
+    plan = tr.plan(n)
+    for write in (lambda: tr.set_plan(n, **plan), lambda: tr.set_chunk(n, tr.chunk(n)), lambda: tr.set_plan(n)):
+        write()
+        assert tr.plan(n) == plan
+        assert [run(host, tr, c, n) for c in counts] == want
+    # any other chunk is taken as it is
+    tr.set_plan(n, chunk=48)
+    assert tr.plan(n)["chunk"] == 48
+    assert [l[2] for l in run(host, tr, 100, n)] == [48, 48, 4]

@@ -319,8 +319,8 @@ int ccpt_drift_filter(const double* r, int n, double a0, double rate_limit, doub
    rather than leave a small one for the end.
    ccpt_autotune times ccpt_track_batch on `batch` frames of size n x n (each
    frame is the context's reference of that size; timing does not depend on
-   content) over chunk sizes and the block plans of ccpt_plan, and keeps the
-   fastest for later calls on this context.  Needs a reference of size n
+   content) in the default launches and over chunk sizes and the block plans of
+   ccpt_plan, and keeps the fastest for later calls on this context.  Needs a reference of size n
    (CCPT_E_NOREF otherwise).  Allocates and synchronises the stream. */
 int ccpt_autotune(ccpt_ctx* ctx, int n, int batch, void* stream);
 

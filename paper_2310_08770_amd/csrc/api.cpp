@@ -1661,7 +1661,11 @@ int ccpt_autotune(ccpt_ctx* ctx, int n, int batch, void* stream) {
   const int saved_flags = ctx->o.flags;
   ctx->o.flags = 0;  // no graphs or profiling while tuning
   ctx->sched[n] = Schedule{};
-  float best = 1e30f;
+  // the default launches first: no chunk stands for them (they may be one launch
+  // where every chunk makes two), and a candidate has to beat them
+  drop_graphs(ctx);
+  float best = time_batch(ctx, rois.data(), batch, out, stream, e0, e1, 3);
+  if (best < 0.f) best = 1e30f;
   tune_shape(ctx, n, batch, rois.data(), batch, out, stream, e0, e1, best);
   ctx->o.flags = saved_flags;
   drop_graphs(ctx);

@@ -27,3 +27,18 @@ def test_a_plan_that_is_read_and_written_back_changes_nothing(host, n, precision
     tr.set_plan(n, chunk=48)
     assert tr.plan(n)["chunk"] == 48
     assert [l[2] for l in run(host, tr, 100, n)] == [48, 48, 4]
+
+
+def test_autotune_keeps_the_default_unless_it_is_beaten(host):
+    # (in the model a launch takes the same time whatever its size, and 900 frames
+    # are one default launch, a quarter over 768: every chunk makes two or more)
+    tr = host.tracker()
+    tr.set_reference(torch.ones(256, 256), stream=0)
+    plan = tr.plan(256)
+    assert tr.autotune(256, 900, stream=0) == plan["chunk"]
+    assert tr.plan(256) == plan
+    host.launches()
+    assert len(run(host, tr, 900, 256)) == 1
+    # two launches beat the three of the default (the first chunk that makes two)
+    tr.autotune(256, 2000, stream=0)
+    assert tr.plan(256)["chunk"] == 1024

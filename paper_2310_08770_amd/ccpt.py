@@ -38,6 +38,9 @@ U16, F32, F64 = 0, 1, 2
 FLAG_GRAPH = 1
 FLAG_PROFILE = 2
 FLAG_STREAMS = 4
+#: Changes with the kernels that launch plans choose between: plans tuned for
+#: others (1: the matrix DFT, whose chunks are too small for these) are not used.
+PLAN_VERSION = 2
 STAGES = ["init", "rows_fwd", "cols", "rows_inv", "updft", "newton", "grad", "xcorr"]
 
 RESULT_DTYPE = np.dtype([
@@ -352,28 +355,30 @@ class Tracker:
         return {STAGES[i]: (ms[i], cnt[i]) for i in range(k)}
 
     def autotune(self, n, batch, stream=None, cache=None):
-        """Tunes the chunk size for n x n frames in batches of `batch` (needs a
-        reference of that size).  With `cache` (a JSON file path) the choice is
-        read from / written to it, keyed by GPU arch, size, u, precision, mode."""
+        """Tunes the launch plan of n x n frames in batches of `batch` (needs a
+        reference of that size); returns its chunk size.  With `cache` (a JSON file
+        path) the plan is read from / written to it, keyed by GPU arch, size, u,
+        precision, mode and PLAN_VERSION."""
         key = None
         if cache:
             import json
             props = torch.cuda.get_device_properties(self.device)
             arch = getattr(props, "gcnArchName", props.name)
             o = self.options
-            key = f"{arch}|N={n}|batch={batch}|u={o.upsample}|prec={o.precision}|mode={o.mode}"
+            key = (f"{arch}|N={n}|batch={batch}|u={o.upsample}|prec={o.precision}|mode={o.mode}"
+                   f"|kernels={PLAN_VERSION}")
             try:
                 with open(cache) as fh:
                     table = json.load(fh)
             except (OSError, ValueError):
                 table = {}
             if key in table:
-                self.set_chunk(n, int(table[key]))
-                return int(table[key])
+                self.set_plan(n, **table[key])
+                return self.chunk(n)
         self._check(lib().ccpt_autotune(self._h, int(n), int(batch), c_void_p(_stream_handle(stream))))
         chunk = self.chunk(n)
         if cache:
-            table[key] = chunk
+            table[key] = self.plan(n)
             with open(cache, "w") as fh:
                 json.dump(table, fh, indent=1, sort_keys=True)
         return chunk

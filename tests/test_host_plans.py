@@ -1,4 +1,7 @@
 """Launch plans and the tuners, by the launches that they lead to."""
+import json
+from types import SimpleNamespace
+
 import pytest
 import torch
 
@@ -42,3 +45,32 @@ def test_autotune_keeps_the_default_unless_it_is_beaten(host):
     # two launches beat the three of the default (the first chunk that makes two)
     tr.autotune(256, 2000, stream=0)
     assert tr.plan(256)["chunk"] == 1024
+
+
+def test_cached_plans_are_whole_and_of_these_kernels(host, monkeypatch, tmp_path):
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: SimpleNamespace(gcnArchName="gfx950", name=""))
+    cache = str(tmp_path / "plans.json")
+    # a chunk kept for other kernels is not applied, and is left in the file
+    old = {"gfx950|N=256|batch=900|u=100|prec=0|mode=0": 16}
+    with open(cache, "w") as fh:
+        json.dump(old, fh)
+
+    def tracker():
+        tr = host.tracker()
+        tr.set_reference(torch.ones(256, 256), stream=0)
+        return tr
+
+    a = tracker()
+    chunk = a.autotune(256, 900, stream=0, cache=cache)
+    assert chunk == a.chunk(256) != 16
+    table = json.load(open(cache))
+    key, = set(table) - set(old)
+    assert table[key] == a.plan(256) and old.items() <= table.items()
+    # every field of a kept plan is applied, without timing anything
+    table[key] = dict(chunk=512, split_blocks=512, fused_min=1)
+    with open(cache, "w") as fh:
+        json.dump(table, fh)
+    b = tracker()
+    host.launches()
+    assert b.autotune(256, 900, stream=0, cache=cache) == 512
+    assert b.plan(256) == table[key] and host.launches() == []

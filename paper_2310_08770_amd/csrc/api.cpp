@@ -183,12 +183,32 @@ int fail(ccpt_ctx* ctx, int code, const char* fmt, ...) {
   return code;
 }
 
+// A failed call is reported by this library's call that made it: its error is
+// taken off the runtime, whose last error the launches read.
 #define HIP_CHECK(ctx, call)                                                               \
   do {                                                                                     \
     hipError_t e_ = (call);                                                                \
-    if (e_ != hipSuccess)                                                                  \
+    if (e_ != hipSuccess) {                                                                \
+      (void)hipGetLastError();                                                             \
       return fail(ctx, CCPT_E_HIP, "%s failed: %s", #call, hipGetErrorString(e_));         \
+    }                                                                                      \
   } while (0)
+
+// Device and pinned host memory; false (p null, no error left) if refused.
+template <typename T>
+bool device_alloc(T*& p, size_t bytes) {
+  if (hipMalloc((void**)&p, bytes) == hipSuccess) return true;
+  (void)hipGetLastError();
+  p = nullptr;
+  return false;
+}
+template <typename T>
+bool pinned_alloc(T*& p, size_t bytes) {
+  if (hipHostMalloc((void**)&p, bytes, hipHostMallocDefault) == hipSuccess) return true;
+  (void)hipGetLastError();
+  p = nullptr;
+  return false;
+}
 
 int set_device(ccpt_ctx* ctx) {
   HIP_CHECK(ctx, hipSetDevice(ctx->device));
@@ -276,10 +296,7 @@ int ensure_ws(ccpt_ctx* ctx, size_t bytes) {
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
   }
-  if (hipMalloc(&ctx->ws, bytes) != hipSuccess) {
-    ctx->ws = nullptr;
-    return fail(ctx, CCPT_E_NOMEM, "workspace of %zu bytes", bytes);
-  }
+  if (!device_alloc(ctx->ws, bytes)) return fail(ctx, CCPT_E_NOMEM, "workspace of %zu bytes", bytes);
   ctx->ws_bytes = bytes;
   return CCPT_OK;
 }
@@ -698,8 +715,7 @@ int upload_desc(ccpt_ctx* ctx, const std::vector<FrameDesc>& desc, hipStream_t s
     ctx->d_desc = nullptr;
     ctx->h_desc = nullptr;
     size_t cap = std::max<size_t>(n, 64);
-    if (hipMalloc(&ctx->d_desc, cap * sizeof(FrameDesc)) != hipSuccess ||
-        hipHostMalloc(&ctx->h_desc, cap * sizeof(FrameDesc), hipHostMallocDefault) != hipSuccess) {
+    if (!device_alloc(ctx->d_desc, cap * sizeof(FrameDesc)) || !pinned_alloc(ctx->h_desc, cap * sizeof(FrameDesc))) {
       ctx->desc_cap = 0;
       return fail(ctx, CCPT_E_NOMEM, "descriptor table");
     }
@@ -727,10 +743,7 @@ int ensure_buf(ccpt_ctx* ctx, void*& p, size_t& cap, size_t bytes) {
     p = nullptr;
     cap = 0;
   }
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    p = nullptr;
-    return fail(ctx, CCPT_E_NOMEM, "buffer of %zu bytes", bytes);
-  }
+  if (!device_alloc(p, bytes)) return fail(ctx, CCPT_E_NOMEM, "buffer of %zu bytes", bytes);
   cap = bytes;
   return CCPT_OK;
 }
@@ -966,10 +979,9 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
     if (r.n != code) {
       free_ref(r);
       r.n = code;
-      if (hipMalloc(&r.spec, spec * sizeof(float2)) != hipSuccess ||
-          hipMalloc(&r.img, npx * sizeof(float)) != hipSuccess ||
-          (fp64(ctx) && hipMalloc(&r.spec64, spec * sizeof(double2)) != hipSuccess) ||
-          (weight && hipMalloc(&r.espec, spec * sizeof(float2)) != hipSuccess)) {
+      if (!device_alloc(r.spec, spec * sizeof(float2)) || !device_alloc(r.img, npx * sizeof(float)) ||
+          (fp64(ctx) && !device_alloc(r.spec64, spec * sizeof(double2))) ||
+          (weight && !device_alloc(r.espec, spec * sizeof(float2)))) {
         drop_from(i);
         return fail(ctx, CCPT_E_NOMEM, "reference spectra");
       }
@@ -1061,7 +1073,6 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
   if (!small) {
     rc = ensure_ws(ctx, ows[nl]);
     if (rc == CCPT_E_NOMEM) {
-      (void)hipGetLastError();  // the refused allocation is not a launch's error
       ctx->ws_refused = ows[nl];
       small = true;
     }
@@ -1305,7 +1316,7 @@ int ccpt_track_grad(ccpt_ctx* ctx, const ccpt_roi* rois, int n, const ccpt_resul
     if (ctx->h_small) (void)hipHostFree(ctx->h_small);
     ctx->h_small = nullptr;
     ctx->h_small_cap = 0;
-    if (hipHostMalloc(&ctx->h_small, small_bytes, hipHostMallocDefault) != hipSuccess)
+    if (!pinned_alloc(ctx->h_small, small_bytes))
       return fail(ctx, CCPT_E_NOMEM, "pinned staging");
     ctx->h_small_cap = small_bytes;
   }

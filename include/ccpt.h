@@ -314,9 +314,10 @@ int ccpt_drift_filter(const double* r, int n, double a0, double rate_limit, doub
 /* Launch scheduling of the batched path (a10): frames of one size are run in
    chunks; the chunk size trades the spectra's residency in the Infinity Cache
    against the number of launches and their uneven last rounds of blocks.  The
-   default is 768 frames (more for small ones; at most 2 GB of workspace, 192 MB
-   where the card has no room for that), and a chunk may take a quarter more
-   rather than leave a small one for the end.
+   default is 768 frames (more for small ones; at most 2 GB of workspace), and a
+   chunk may take a quarter more rather than leave a small one for the end; each
+   lane and each of two streams has a workspace of its own.  Where the card has no
+   room for that, calls take chunks of 192 MB until it has.
    ccpt_autotune times ccpt_track_batch on `batch` frames of size n x n (each
    frame is the context's reference of that size; timing does not depend on
    content) in the default launches and over chunk sizes and the block plans of

@@ -110,6 +110,8 @@ struct ccpt_ctx {
   // workspace
   char* ws = nullptr;
   size_t ws_bytes = 0;
+  size_t ws_refused = ~(size_t)0;  // the last workspace that the card had no room for
+  size_t ws_room = 0;              // what it had then
   // descriptors
   FrameDesc* d_desc = nullptr;
   FrameDesc* h_desc = nullptr;
@@ -128,7 +130,6 @@ struct ccpt_ctx {
   hipStream_t cur_stream = nullptr;
   hipEvent_t open_ev = nullptr;
   // adjoint: packed-gradient offsets + accumulator pointers, accumulators
-  size_t ws_refused = ~(size_t)0;  // a workspace that the card had no room for
   void* gsmall = nullptr;
   size_t gsmall_cap = 0;
   char* h_small = nullptr;
@@ -287,7 +288,10 @@ void drop_graphs(ccpt_ctx* ctx) {
   ctx->graphs.clear();
 }
 
-int ensure_ws(ccpt_ctx* ctx, size_t bytes) {
+// A workspace of at least `bytes`.  CCPT_E_NOMEM (no workspace; not recorded as
+// the context's error) if it was not given, `why` the runtime's reason.
+int grow_ws(ccpt_ctx* ctx, size_t bytes, hipError_t& why) {
+  why = hipSuccess;
   if (bytes <= ctx->ws_bytes) return CCPT_OK;
   drop_graphs(ctx);
   if (ctx->ws) {
@@ -296,9 +300,44 @@ int ensure_ws(ccpt_ctx* ctx, size_t bytes) {
     ctx->ws = nullptr;
     ctx->ws_bytes = 0;
   }
-  if (!device_alloc(ctx->ws, bytes)) return fail(ctx, CCPT_E_NOMEM, "workspace of %zu bytes", bytes);
+  why = hipMalloc(&ctx->ws, bytes);
+  if (why != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->ws = nullptr;
+    return CCPT_E_NOMEM;
+  }
   ctx->ws_bytes = bytes;
+  if (bytes >= ctx->ws_refused) ctx->ws_refused = ~(size_t)0;
   return CCPT_OK;
+}
+
+int ensure_ws(ccpt_ctx* ctx, size_t bytes) {
+  hipError_t why;
+  const int rc = grow_ws(ctx, bytes, why);
+  return rc == CCPT_E_NOMEM ? fail(ctx, rc, "workspace of %zu bytes", bytes) : rc;
+}
+
+// A workspace that the call can do without: as grow_ws, but one that was refused
+// is asked for again only when the card has more room than it had then (asking
+// gives up the workspace in hand), and never while the stream is captured.
+int ask_ws(ccpt_ctx* ctx, size_t bytes, hipStream_t s) {
+  size_t left = 0, total = 0;
+  if (bytes > ctx->ws_bytes && bytes >= ctx->ws_refused) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(s, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
+                       hipMemGetInfo(&left, &total) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    left += ctx->ws_bytes;
+    if (!known || left <= ctx->ws_room || left < bytes) return CCPT_E_NOMEM;
+  }
+  hipError_t why;
+  const int rc = grow_ws(ctx, bytes, why);
+  if (why == hipErrorOutOfMemory) {
+    ctx->ws_refused = bytes;
+    if (hipMemGetInfo(&left, &total) != hipSuccess) (void)hipGetLastError();
+    ctx->ws_room = left;
+  }
+  return rc;
 }
 
 // Half-spectrum elements of one frame (shape code).
@@ -1066,17 +1105,10 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
       ost[l + 1] = ost[l] + lst[l] * nslots;
     }
   };
-  // a card with no room for the launches' workspace takes smaller ones, from then
-  // on without asking again (asking gives up the workspace in hand)
+  // a card with no room for the launches' workspace takes smaller ones
   layout(false);
-  bool small = ows[nl] >= ctx->ws_refused;
-  if (!small) {
-    rc = ensure_ws(ctx, ows[nl]);
-    if (rc == CCPT_E_NOMEM) {
-      ctx->ws_refused = ows[nl];
-      small = true;
-    }
-  }
+  rc = ask_ws(ctx, ows[nl], s);
+  const bool small = rc == CCPT_E_NOMEM;
   if (small) {
     layout(true);
     rc = ensure_ws(ctx, ows[nl]);

@@ -18,6 +18,7 @@ struct Record {
 };
 
 size_t g_limit = ~(size_t)0, g_live = 0;
+int g_asked = 0;  // device allocations asked for
 std::map<void*, size_t> g_size;
 hipError_t g_last = hipSuccess;  // kept until it is read, as the runtime does
 std::vector<Record> g_log;
@@ -49,6 +50,7 @@ extern "C" {
 // ---- controls of the tests
 void host_limit(size_t bytes) { g_limit = bytes; }
 size_t host_live() { return g_live; }
+int host_asked() { return g_asked; }
 void host_last_error_clear() { g_last = hipSuccess; }
 int host_no_tables64() { return g_no_tables64; }
 int host_log(int* out, int cap) {  // (ny, nx, count, fused_min, pairs_ok) each; empties the log
@@ -61,6 +63,7 @@ int host_log(int* out, int cap) {  // (ny, nx, count, fused_min, pairs_ok) each;
 
 // ---- runtime
 hipError_t hipMalloc(void** p, size_t bytes) {
+  ++g_asked;
   if (bytes > g_limit || g_live > g_limit - bytes) return err(hipErrorOutOfMemory);
   *p = malloc(bytes ? bytes : 1);
   g_size[*p] = bytes;

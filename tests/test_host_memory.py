@@ -1,5 +1,7 @@
 """Calls on a card that has no room: what they report, and that the calls after
 them are as if they had not been made."""
+import ctypes
+
 import pytest
 import torch
 
@@ -63,3 +65,58 @@ def test_refused_buffers_of_other_calls(host):
         host.limit(2**63)
         tr.track(fr, stream=0)
         call()
+
+
+# 192 MB by a 512 x 512 frame's two FP32 half spectra
+SMALL = (192 << 20) // (2 * 512 * 257 * 8)
+
+
+def counts(host):
+    return [l[2] for l in host.launches()]
+
+
+def test_smaller_launches_without_room_and_default_ones_with_it(host):
+    tr = host.tracker()
+    tr.set_reference(torch.ones(512, 512), stream=0)
+    call = frames(200, 512)
+    tr.track(call[0][:1], [0], stream=0)
+    assert counts(host) == [1]
+    host.limit(host.live() + (300 << 20))
+    tr.track(*call, stream=0)
+    assert counts(host) == [SMALL, SMALL, 200 - 2 * SMALL]
+    # the call succeeded: no error is left of the workspace it did without
+    assert host.lib.ccpt_last_error(tr._h, None, 0) == 0
+    # the same room: not asked again
+    asked = host.asked()
+    for _ in range(3):
+        tr.track(*call, stream=0)
+        assert counts(host) == [SMALL, SMALL, 200 - 2 * SMALL]
+    assert host.asked() == asked
+    # more room while the stream is captured: allocations have to wait
+    host.limit(2**63)
+    graph = ctypes.c_void_p()
+    host.lib.hipStreamBeginCapture(None, 0)
+    tr.track(*call, stream=0)
+    host.lib.hipStreamEndCapture(None, ctypes.byref(graph))
+    host.lib.hipGraphDestroy(graph)
+    assert host.asked() == asked
+    # and after it: the default launches again
+    tr.track(*call, stream=0)
+    assert counts(host) == [200]
+    assert host.lib.ccpt_last_error(tr._h, None, 0) == 0
+
+
+def test_a_workspace_in_hand_is_used(host):
+    # a larger call was refused; one that fits what the context has is not affected
+    tr = host.tracker()
+    tr.set_reference(torch.ones(512, 512), stream=0)
+    tr.track(*frames(150, 512), stream=0)
+    assert counts(host) == [150]
+    host.limit(host.live() + (1 << 20))
+    tr.track(*frames(200, 512), stream=0)  # refused; the small launches' workspace instead
+    assert counts(host) == [SMALL, SMALL, 200 - 2 * SMALL]
+    host.limit(2**63)
+    tr.track(*frames(150, 512), stream=0)
+    assert counts(host) == [150]
+    tr.track(*frames(200, 512), stream=0)
+    assert counts(host) == [200]

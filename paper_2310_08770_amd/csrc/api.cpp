@@ -234,10 +234,17 @@ double step_limit(const ccpt_ctx* ctx) {
   return fp64(ctx) ? grid : std::max(grid, 0.5 * ctx->o.window);
 }
 
+// A device copy of src; dst stays null if it fails.
 template <typename T>
 int upload(ccpt_ctx* ctx, T*& dst, const std::vector<T>& src) {
-  HIP_CHECK(ctx, hipMalloc(&dst, src.size() * sizeof(T)));
-  HIP_CHECK(ctx, hipMemcpy(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+  T* p = nullptr;
+  HIP_CHECK(ctx, hipMalloc(&p, src.size() * sizeof(T)));
+  if (hipMemcpy(p, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(p);
+    return fail(ctx, CCPT_E_HIP, "copying a table to the device failed");
+  }
+  dst = p;
   return CCPT_OK;
 }
 
@@ -268,10 +275,10 @@ int ensure_tables(ccpt_ctx* ctx, int code) {
   if (!rc) rc = upload(ctx, t.gx, h.gx);
   if (!rc) rc = upload(ctx, t.gxn, h.gxn);
   if (!rc && fp64(ctx)) rc = upload(ctx, t.tw64, tw);
-  if (!rc && !ctx->tf) {
+  // the grid's tables, once per context: in FP64 in the FP64 mode, else in FP32
+  if (!rc && !ctx->tf && !ctx->td) {
     const GridTables g = build_grid_tables(ctx->o.upsample, ctx->M, ctx->c, ctx->half);
-    rc = upload(ctx, ctx->tf, g.tf);
-    if (!rc) rc = upload(ctx, ctx->td, g.td);
+    rc = fp64(ctx) ? upload(ctx, ctx->td, g.td) : upload(ctx, ctx->tf, g.tf);
   }
   if (rc) {
     free_tables(t);

@@ -55,8 +55,9 @@ def host(host_lib, monkeypatch):
     L.host_limit(2**63)
     L.host_last_error_clear()
     launches()
-    yield SimpleNamespace(tracker=tracker, launches=launches, limit=L.host_limit, live=L.host_live, asked=L.host_asked, lib=L,
-                          no_tables64=L.host_no_tables64)
+    yield SimpleNamespace(tracker=tracker, launches=launches, limit=L.host_limit, live=L.host_live, asked=L.host_asked, refuse=L.host_refuse, lib=L,
+                          no_tables=L.host_no_tables)
     L.host_limit(2**63)
+    L.host_refuse(0)
     for tr in made:
         tr.close()

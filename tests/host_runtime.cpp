@@ -18,13 +18,14 @@ struct Record {
 };
 
 size_t g_limit = ~(size_t)0, g_live = 0;
-int g_asked = 0;  // device allocations asked for
+int g_asked = 0;           // device allocations asked for
+int g_refuse = 0;          // > 0: the allocation that many from now is refused
 std::map<void*, size_t> g_size;
 hipError_t g_last = hipSuccess;  // kept until it is read, as the runtime does
 std::vector<Record> g_log;
 std::vector<Record>* g_capture = nullptr;
 double g_ms_launch = 1.0, g_ms = 0.0;  // simulated time of a correlation launch, and now
-bool g_no_tables64 = false;            // a window launch in FP64 without its FP64 grid table
+bool g_no_tables = false;  // a window launch without its grid table
 
 hipError_t err(hipError_t e) {
   if (e != hipSuccess) g_last = e;
@@ -51,8 +52,9 @@ extern "C" {
 void host_limit(size_t bytes) { g_limit = bytes; }
 size_t host_live() { return g_live; }
 int host_asked() { return g_asked; }
+void host_refuse(int k) { g_refuse = k; }
 void host_last_error_clear() { g_last = hipSuccess; }
-int host_no_tables64() { return g_no_tables64; }
+int host_no_tables() { return g_no_tables; }
 int host_log(int* out, int cap) {  // (ny, nx, count, fused_min, pairs_ok) each; empties the log
   int n = 0;
   for (const Record& r : g_log)
@@ -64,7 +66,7 @@ int host_log(int* out, int cap) {  // (ny, nx, count, fused_min, pairs_ok) each;
 // ---- runtime
 hipError_t hipMalloc(void** p, size_t bytes) {
   ++g_asked;
-  if (bytes > g_limit || g_live > g_limit - bytes) return err(hipErrorOutOfMemory);
+  if ((g_refuse > 0 && --g_refuse == 0) || bytes > g_limit || g_live > g_limit - bytes) return err(hipErrorOutOfMemory);
   *p = malloc(bytes ? bytes : 1);
   g_size[*p] = bytes;
   g_live += bytes;
@@ -189,7 +191,7 @@ int launch_xcorr64(int n, const GroupParams& g, hipStream_t, const Marker&) {
 }
 int launch_window_coef(int, int, const GroupParams&, const WindowTables&, int, hipStream_t) { return status(); }
 int launch_window_max(int, int, const GroupParams& g, const WindowTables& t, int, double, hipStream_t) {
-  if (g.X64 && !t.td) g_no_tables64 = true;
+  if (!(g.X64 ? (const void*)t.td : (const void*)t.tf)) g_no_tables = true;
   return status();
 }
 int launch_init_state(FrameState*, int, hipStream_t) { return status(); }

@@ -120,3 +120,33 @@ def test_a_workspace_in_hand_is_used(host):
     assert counts(host) == [150]
     tr.track(*frames(200, 512), stream=0)
     assert counts(host) == [200]
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+def test_tables_are_whole_or_absent(host, precision):
+    # each allocation of the first set_reference refused in turn, then the same call
+    from paper_2310_08770_amd import CcptError
+    k = 0
+    while True:
+        k += 1
+        tr = host.tracker(precision=precision)
+        host.refuse(k)
+        try:
+            tr.set_reference(torch.ones(64, 64), stream=0)
+        except CcptError as e:
+            assert e.code in (E_NOMEM, E_HIP)
+        else:
+            break
+        tr.set_reference(torch.ones(64, 64), stream=0)
+        tr.track(*frames(3, 64), stream=0)
+        assert not host.no_tables(), k
+    assert k > 5
+
+
+def test_a_context_makes_the_grid_table_it_reads(host):
+    m = 1536  # grid points per axis: 16 floats each in FP32, 24 doubles in FP64
+    for precision, grid in (("fp32", m * 16 * 4), ("fp64", m * 24 * 8)):
+        tr = host.tracker(precision=precision, upsample=1024)
+        before = host.live()
+        tr.set_reference(torch.ones(16, 16), stream=0)
+        assert grid <= host.live() - before < grid + (32 << 10)

@@ -11,9 +11,9 @@
  * maximum of the circular cross-correlation F^-1[F[I] conj F[E]]; for shot
  * noise (CC-SN, Eq. 5-7) it is the extremum of the correlation of (I+eps)^2
  * with 1/(E+eps).  The integer maximum is refined on a 1.5-pixel window
- * sampled at 1.5u points per axis by a matrix-multiply DFT (Sec. III, first
- * paragraph), whose maximum is the paper's sub-pixel estimate; the library
- * then refines it in FP64 by Newton steps on the band-limited correlation.
+ * sampled at 1.5u points per axis (Sec. III, first paragraph), whose maximum
+ * is the paper's sub-pixel estimate; the library then refines it in FP64 by
+ * Newton steps on the band-limited correlation.
  *
  * Conventions used throughout:
  *  - pixels, (y, x) order, row-major images with a row pitch in elements;
@@ -29,9 +29,9 @@
  * N = 2^a 3^b, a >= 1, 16 <= N <= 512, and the rectangles of the paper's
  * Table I, 256x128, 512x256 and 1024x128, in either orientation (the
  * longer side as rows or as columns).  Rectangles are tracked by
- * ccpt_set_reference / ccpt_track_batch in FP32 and BF16X2 precision; the
- * adjoint, the Fisher information, the reference updates and the FP64
- * precision take square frames only.  Other shapes, and rectangles where
+ * ccpt_set_reference / ccpt_track_batch / ccpt_track_update in FP32 and
+ * BF16X2 precision; the adjoint, the Fisher information, the offline
+ * reference and the FP64 precision take square frames only.  Other shapes, and rectangles where
  * only squares are taken, return CCPT_E_UNSUPPORTED.
  *
  * Rectangles: the Nyquist conventions above apply per axis (N/2 of that
@@ -42,7 +42,7 @@
  * Memory: every image/frame pointer, `out`, the gradient inputs and
  * outputs are DEVICE pointers owned by the caller.  The small descriptor
  * arrays (ccpt_image, ccpt_roi) are HOST arrays, read during the call.
- * The context owns reference spectra, DFT tables, workspaces, captured
+ * The context owns reference spectra, window tables, workspaces, captured
  * graphs and the tuning table.
  *
  * Streams: `stream` is a hipStream_t (NULL = the null stream).  Track and

@@ -1,4 +1,4 @@
-// Host side of libccpt: argument checking, reference spectra, DFT tables,
+// Host side of libccpt: argument checking, reference spectra, window tables,
 // workspaces, the per-size launch sequence, graph capture and tuning.
 #include <hip/hip_runtime.h>
 
@@ -144,10 +144,9 @@ struct ccpt_ctx {
   bool st_dirty = true;
   // chunk slots: a group of several chunks runs them alternately on the
   // caller's stream and `aux`, each slot with its own part of the workspace
-  // and frame states (strides below, per slot)
+  // and frame states (CallMem's strides)
   hipStream_t aux = nullptr;
   hipEvent_t fork_evt = nullptr, join_evt = nullptr;
-  size_t slot_ws = 0, slot_st = 0;
   // concurrent size groups: lane 0 is the caller's stream, lanes 1.. these
   // context-owned streams (default priority), forked from and joined back
   // into the caller's stream by events; each lane has its own workspace and
@@ -217,9 +216,6 @@ int set_device(ccpt_ctx* ctx) {
 }
 
 bool fp64(const ccpt_ctx* ctx) { return ctx->o.precision == CCPT_PREC_FP64; }
-bool split(const ccpt_ctx* ctx) {
-  return ctx->o.precision == CCPT_PREC_BF16X2 || ctx->o.precision == CCPT_PREC_FP16X2;
-}
 
 // Longest Newton step before the result falls back to the grid estimate.
 // An FP64 grid locates the maximum to a grid step, so a longer step means
@@ -434,7 +430,7 @@ int window_parts(const ccpt_ctx* ctx, int n, int count) {
 }
 
 int fused_min_for(const ccpt_ctx* ctx, int n) {
-  // the fp16 split takes its operands from the one-kernel correlation only
+  // this precision is defined by the one-kernel correlation, for any launch size
   if (ctx->o.precision == CCPT_PREC_FP16X2) return 1;
   auto it = ctx->sched.find(n);
   if (it != ctx->sched.end() && it->second.fused_min >= 0) return it->second.fused_min;
@@ -504,9 +500,7 @@ struct CallMem {
 CallMem ctx_mem(ccpt_ctx* ctx) {
   CallMem m;
   m.ws = ctx->ws;
-  m.slot_ws = ctx->slot_ws;
   m.st = ctx->st_buf;
-  m.slot_st = ctx->slot_st;
   m.st_dirty = &ctx->st_dirty;
   return m;
 }
@@ -557,7 +551,7 @@ double pixel(const void* raw, int dtype, size_t k) {
 }
 
 // Calls that work on square frames only (the adjoint, the Fisher information
-// and the reference updates).
+// and the offline reference).
 int require_square(ccpt_ctx* ctx, int ny, int nx, const char* what) {
   if (ny != nx)
     return fail(ctx, CCPT_E_UNSUPPORTED, "%s: %dx%d frames are tracked, but this call takes square "
@@ -623,7 +617,6 @@ bool use_slots(const ccpt_ctx* ctx) {
          !(ctx->o.flags & CCPT_FLAG_PROFILE);
 }
 
-// Launches the whole tracking sequence for one size group, chunk by chunk.
 // Frames first..first+count-1 of a plan are uint16 or float32 with an even
 // pitch and pixel pairs aligned to their size.
 bool pairs_ok(const std::vector<FrameDesc>& desc, int first, int count) {
@@ -636,6 +629,7 @@ bool pairs_ok(const std::vector<FrameDesc>& desc, int first, int count) {
   return true;
 }
 
+// Launches the whole tracking sequence for one size group, chunk by chunk.
 int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc, int first,
               int count, ccpt_result* out, hipStream_t s, bool pairs) {
   int limit = 0;
@@ -692,7 +686,6 @@ int run_group(ccpt_ctx* ctx, const CallMem& mem, int n, const FrameDesc* d_desc,
   return CCPT_OK;
 }
 
-
 // Validated, size-grouped descriptors of a roi array.
 struct Plan {
   std::vector<FrameDesc> desc;  // grouped by shape, largest first
@@ -741,7 +734,7 @@ int plan_rois(ccpt_ctx* ctx, const ccpt_roi* rois, int n, Plan& plan, bool fp32_
     }
     plan.sig.back()++;
   }
-  // the fp16 split runs the one-kernel correlation only, which reads pixel pairs
+  // FP16X2 runs the one-kernel correlation only, which reads pixel pairs
   if (ctx->o.precision == CCPT_PREC_FP16X2 && !fp32_spec && !pairs_ok(plan.desc, 0, n))
     return fail(ctx, CCPT_E_UNSUPPORTED,
                 "the fp16 split takes uint16 or float32 frames with an even pitch and aligned pairs");
@@ -1121,10 +1114,8 @@ int ccpt_track_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result* ou
     rc = ensure_ws(ctx, ows[nl]);
   }
   if (rc) return rc;
-  ctx->slot_ws = lws[0];
   rc = ensure_state(ctx, ost[nl], s);
   if (rc) return rc;
-  ctx->slot_st = lst[0];
   rc = upload_desc(ctx, plan.desc, s);
   if (rc) return rc;
 
@@ -1206,7 +1197,7 @@ int ccpt_track_batch_static(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_res
   if (rc) return rc;
   // scratch layout: descriptors | frame states of one chunk | chunk workspace
   const size_t desc_bytes = ((size_t)n * sizeof(FrameDesc) + 255) / 256 * 256;
-  constexpr size_t kStates = 4096;  // the largest chunk of any schedule
+  constexpr size_t kStates = 4096;  // the most frames of a launch here (mem.slot_st limits it)
   const size_t st_bytes = (kStates * sizeof(FrameState) + 255) / 256 * 256;
   CallMem mem;
   mem.st = (FrameState*)(base + desc_bytes);
@@ -1642,8 +1633,8 @@ static float time_batch(ccpt_ctx* ctx, const ccpt_roi* rois, int n, ccpt_result*
 }
 
 // Coordinate search over the launch plan of one shape code: chunk sizes, then
-// the block plans that apply to the shape (FP32 split-K threshold; for
-// 256x256 the one-kernel correlation threshold), then chunk sizes again if
+// the block plans that apply to the shape (the threshold of the split window
+// expansion; for 256x256 the one-kernel correlation's), then chunk sizes again if
 // a block plan changed; every candidate timed on the whole call.
 static void tune_shape(ccpt_ctx* ctx, int code, int count, const ccpt_roi* rois, int n,
                        ccpt_result* out, void* stream, hipEvent_t e0, hipEvent_t e1,

@@ -31,13 +31,13 @@ struct FrameState {
   unsigned long long second_key;  // runner-up of the integer-lag correlation, same
                                   // encoding (0 until set; FP32 and split paths)
   unsigned amin, amax;            // order-preserving keys of min/max of A
-  unsigned flags;                 // CCPT_ST_NONFINITE; CCPT_ST_NEAR_TIE (FP64 mode)
+  unsigned flags;                 // CCPT_ST_NONFINITE
   unsigned done;                  // blocks of the frame whose grid share is in grid_key
 };
 
 // FP64 mode: best correlation value of one row block of a frame and its
-// row-major index (ties to the lower index); reduced per frame before the
-// upsampled DFT, since an FP64 value and an index do not fit one 64-bit key.
+// row-major index (ties to the lower index); reduced per frame by the window
+// kernels, since an FP64 value and an index do not fit one 64-bit key.
 struct PeakCand {
   double v;     // best value of the block
   double v2;    // its runner-up value (a value equal to v at another index counts)
@@ -154,21 +154,6 @@ __host__ __device__ inline bool near_tie(double v1, double v2) {
 
 __host__ __device__ inline unsigned key_index(unsigned long long k) {
   return 0xFFFFFFFFu - (unsigned)(k & 0xFFFFFFFFull);
-}
-
-// Tall-image coordinates (y, x) of the integer peak from its frame row-major
-// index q (trans: the index in a wide frame of NX rows of NY pixels); an
-// index that was never set (cannot happen for a tracked frame) reads as 0.
-template <int NY, int NX>
-__device__ __forceinline__ void peak_yx(unsigned q, int trans, int& y, int& x) {
-  if (q >= (unsigned)(NY * NX)) q = 0;
-  if (NY != NX && trans) {
-    y = (int)(q % NY);
-    x = (int)(q / NY);
-  } else {
-    y = (int)(q / NX);
-    x = (int)(q % NX);
-  }
 }
 
 // Frame row-major index of point (my, mx) of the M x M grid of the tall image.

@@ -61,8 +61,9 @@ __device__ __forceinline__ unsigned at(unsigned q, unsigned i) {
 
 // Places of elements i0 + t STEP, t = 0, 1, ..: a constant step from the first
 // for rows and unpadded columns.  In padded columns (powers of two) STEP is a
-// multiple of 16, or a power of two below 16 with i0 mod 16 < STEP (the
-// Stockham write order; pad() then adds as for i0 = 0).
+// multiple of 16, or (the Stockham write order, i0 = k + a BLOCK with k < STEP) a
+// power of two below 16 whose BLOCK, STEP times the radix, divides 16 or is a
+// multiple of it; pad() then adds as for i0 = 0.
 template <int NY, bool ROW, int STEP>
 __device__ __forceinline__ constexpr unsigned step_to(unsigned t) {
   return ROW ? t * STEP * Col<NY>::S : Col<NY>::PAD ? t * STEP + ((t * STEP) >> 4) : t * STEP;

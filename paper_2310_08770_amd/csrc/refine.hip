@@ -13,8 +13,8 @@
 //
 //   exp(i z x) = sum_n (2 - [n = 0]) i^n J_n(z) T_n(x),  x = e / B, z = 2 pi k~ B / N,
 //
-// whose terms fall as (z/2)^n / n!: 24 of them leave less than 2 J_24(pi B),
-// 1e-17 at B = 1.05 (the widest window) and 1e-19 at the paper's 1.5 px.  So
+// whose terms fall as (z/2)^n / n!: 24 of them leave about 2 J_24(pi B),
+// 5e-19 at B = 1.05 (the widest window) and 7e-22 at the paper's 1.5 px.  So
 //
 //   C(p + e) = sum_{n, m < 24} c[n][m] T_n(ey / B) T_m(ex / B)
 //
@@ -481,12 +481,15 @@ constexpr int kMaxPasses = 3;
 // Grid: one block of four waves per frame, or (few frames) nb blocks, each
 // over its share of the 32-column strips of the grid, the last of them to
 // finish going on to Newton.  A wave takes a strip: V[n][mx] =
-// sum_m c[n][m] T_m(x_mx) in registers (16 terms: the series beyond is under
-// 1e-10 of C, below FP32), then U = T V row tile by row tile on 32x32x2 FP32
+// sum_m c[n][m] T_m(x_mx) in registers (16 terms: what they leave out is about
+// 2 J_16(pi B) of the sum of |X|, 3e-12 at the paper's 1.5 px and 2.4e-10 at the
+// widest window, below FP32), then U = T V row tile by row tile on 32x32x2 FP32
 // matrix instructions (8 per 1024 grid points) with the running maximum per
 // lane.  c is scaled by a power of two and its constant
 // (the largest term, which moves no maximum) is dropped before the rounding
 // to FP32.  The FP64 mode does the same with 24 terms on 16x16x4 FP64.
+// The FP32 instance has 84 bytes of scratch a lane: one spilled register and the
+// call of direct_eval.
 // Bound by the serial chain of a frame (coefficients, grid, maximum, Newton's
 // FP64 steps), not by the grid's matrix work (busy 0.24): 10,000 frames of 256 x
 // 256, u = 100, in launches of 768 take 0.32 ms; one frame takes 14 us, against 26 us for the second half of
@@ -850,6 +853,8 @@ __global__ void __launch_bounds__(kMThreads, sizeof(CX) == sizeof(float2) ? 3 : 
 template <typename CX>
 static int coef_x(int ny, int nx, const GroupParams& g, const WindowTables& t, int nparts, hipStream_t s) {
   const int ntile = (nx / 2 + 15) / 16;
+  // (in FP64 two tiles a wave need 27 registers more than there are, 112 bytes of
+  // scratch a lane; one tile needs none)
   // tiles per wave and waves per group: the split whose busiest wave has the
   // fewest k steps (the second contraction counts as four for each tile);
   // among equals two tiles at a time, which share the table values of a k step

@@ -5,8 +5,8 @@
 // The 2-D transforms are split into a row pass (each row of N reals is
 // packed as N/2 complex values, transformed, and unpacked into N/2+1 bins)
 // and a column pass over the N/2+1 columns.  Both passes keep their data in
-// LDS and exchange it through a per-frame workspace that stays in the
-// L2/Infinity-Cache for the chunk sizes used.
+// LDS and exchange it through a per-frame workspace, which launches of a few
+// frames find in the L2/Infinity Cache; default launches (up to 2.5 GB) do not.
 //
 // Bound by memory latency and, at 512 x 512, by T's and X's traffic through HBM.
 // Every value that a thread moves is requested before the first is used, places
@@ -841,9 +841,7 @@ int launch_xcorr(int ny, int nx, const GroupParams& g0, hipStream_t s, const Mar
   if (nl > 0) {
     GroupParams a = g0;
     a.count = nl;
-    mark(CCPT_STAGE_XCORR, 1);
     const int rc = launch_xcorr_lds(ny, nx, a, s);
-    mark(CCPT_STAGE_XCORR, 0);
     if (rc || nl == g0.count) return rc;
   }
   GroupParams g = g0;  // the frames that are left

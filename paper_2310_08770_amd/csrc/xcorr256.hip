@@ -27,8 +27,10 @@
 // own.  The correlation comes out as half the unnormalised 2-D inverse (the
 // scale does not move the maximum).
 //
-// Bound by VALU issue: LDS leaves a CU one block, two waves per SIMD; leaving out the
-// reference reads, the LDS reads or the frame loads gains only 3, 2 and 10 %.
+// LDS leaves a CU one block, two waves per SIMD, whose VALU instructions fill
+// about 0.6 of the issue slots (0.30 of each wave's life); the rest is the waits
+// that two waves do not hide.  Leaving out the reference reads, the LDS reads or
+// the frame loads gains only 3, 2 and 10 %.
 // 768 frames (three blocks per CU) take 177 us; 183 before non-negative pixels
 // compared float bits instead of keys, indexes were looked up only by threads
 // that hold the maximum, offsets were 32-bit and wave-local exchanges dropped

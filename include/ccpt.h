@@ -199,7 +199,9 @@ void ccpt_destroy(ccpt_ctx* ctx);
    B = E (CC-U) or B = -1/(E+eps) (CC-SN, Eq. 7), transforms it and keeps
    conj F[B] resident.  References may have different sizes; ids are
    0..n_refs-1.  Synchronises `stream`.  Errors: CCPT_E_INVALID,
-   CCPT_E_UNSUPPORTED, CCPT_E_NONPOSITIVE_REF (CC-SN, any E + eps <= 0). */
+   CCPT_E_UNSUPPORTED, CCPT_E_NONPOSITIVE_REF (CC-SN, any E + eps <= 0): the
+   earlier set stays; CCPT_E_NOMEM, CCPT_E_HIP: it may be gone, and then the
+   context has no references. */
 int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* stream);
 
 /* Tracks n frames (Sec. II Eq. 4/7 and Sec. III): for each roi i computes

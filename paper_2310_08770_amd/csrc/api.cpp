@@ -1000,11 +1000,17 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
   if (rc) return rc;
   float2* T = (float2*)ctx->ref_tmp;
   double2* T64 = (double2*)ctx->ref_tmp;
-  // a reference of the same shape takes over its predecessor's buffers; from
-  // the first failure on there are no references
+  // a reference of the same shape takes over its predecessor's buffers; after a
+  // failure there are no references: some of the new set among what a caller
+  // takes for the old one would have other sizes than its gradient arrays
   auto drop_from = [&](size_t k) {
     for (size_t r = k; r < ctx->refs.size(); ++r) free_ref(ctx->refs[r]);
     ctx->refs.resize(std::min(k, ctx->refs.size()));
+  };
+  auto lost = [&](int code, const char* what) {
+    if (hipStreamSynchronize(s) != hipSuccess) (void)hipGetLastError();
+    drop_from(0);
+    return fail(ctx, code, "%s", what);
   };
   drop_from(n_refs);
   const int weight = ctx->o.mode == CCPT_MODE_CCSN ? 1 : 0;
@@ -1020,10 +1026,8 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
       r.n = code;
       if (!device_alloc(r.spec, spec * sizeof(float2)) || !device_alloc(r.img, npx * sizeof(float)) ||
           (fp64(ctx) && !device_alloc(r.spec64, spec * sizeof(double2))) ||
-          (weight && !device_alloc(r.espec, spec * sizeof(float2)))) {
-        drop_from(i);
-        return fail(ctx, CCPT_E_NOMEM, "reference spectra");
-      }
+          (weight && !device_alloc(r.espec, spec * sizeof(float2))))
+        return lost(CCPT_E_NOMEM, "reference spectra");
     }
     const int ny = code_ny(code), nx = code_nx(code), tr = code_trans(code);
     // the context's float copy is stored as given (pitch nx), a wide one read
@@ -1035,11 +1039,8 @@ int ccpt_set_reference(ccpt_ctx* ctx, const ccpt_image* refs, int n_refs, void* 
                         st.tw, s) ||
         (weight && launch_spectrum(ny, nx, r.img, CCPT_F32, im.nx, 0, tr, 1, 0, 0.f, 0, T, r.espec, st.tw, s)) ||
         (fp64(ctx) && launch_spectrum64(im.nx, im.data, im.dtype, im.pitch, 0, 1, weight, ctx->o.eps, 1, T64,
-                                        r.spec64, st.tw64, s))) {
-      (void)hipStreamSynchronize(s);
-      drop_from(i);
-      return fail(ctx, CCPT_E_HIP, "reference spectrum launch failed");
-    }
+                                        r.spec64, st.tw64, s)))
+      return lost(CCPT_E_HIP, "reference spectrum launch failed");
   }
   HIP_CHECK(ctx, hipStreamSynchronize(s));
   return CCPT_OK;

@@ -7,7 +7,7 @@ import torch
 
 from tests._host import host, host_lib  # noqa: F401
 
-E_NOMEM, E_HIP = -6, -4
+E_NOREF, E_NOMEM, E_HIP = -3, -6, -4
 
 
 def refused(call, codes=(E_NOMEM,)):
@@ -150,3 +150,26 @@ def test_a_context_makes_the_grid_table_it_reads(host):
         before = host.live()
         tr.set_reference(torch.ones(16, 16), stream=0)
         assert grid <= host.live() - before < grid + (32 << 10)
+
+
+def test_a_set_that_fails_leaves_no_part_of_it(host):
+    # two larger references, each allocation refused in turn: a caller that still
+    # holds the old set sizes its gradient arrays by it
+    fr = torch.zeros(3, 512, 512)
+    g = torch.ones(3, 2, dtype=torch.float64)
+    fwd = torch.zeros(3, 72, dtype=torch.uint8)
+    k = 0
+    while True:
+        k += 1
+        tr = host.tracker()
+        tr.set_reference(torch.ones(16, 16), stream=0)
+        host.refuse(k)
+        try:
+            tr.set_reference([torch.ones(512, 512), torch.ones(512, 512)], stream=0)
+        except Exception:
+            host.refuse(0)
+            # (the old set, of another size, or none)
+            refused(lambda: tr.track_grad(fr, fwd, g, stream=0), (E_NOREF, -1))
+        else:
+            break
+    assert k > 5

@@ -11,8 +11,9 @@
 // correlation have the same bits on either path; which one a frame takes
 // (lds_frames) is a matter of time only.
 //
-// Bound by VALU issue (address arithmetic and butterflies, about 3400
-// instructions per wave at 128 x 128) and the LDS passes.  us for the stage,
+// Bound by VALU issue (address arithmetic and butterflies, about 3100
+// instructions per wave at 128 x 128, which take 0.65 to 0.8 of the issue slots)
+// and the waits on the LDS passes.  us for the stage,
 // three passes -> one kernel: 1024 frames of 64 x 64 63 -> 21, 96 x 96 114 -> 52, 128 x 128
 // 143 -> 65, 192 x 192 323 -> 254, 256 x 128 306 -> 182; one frame of 64 x 64
 // 22 -> 10, of 128 x 128 24 -> 22.
